@@ -2,6 +2,7 @@
 // scratch memory and the launch sequence on the caller's stream.
 #include "../../include/mdgemm.h"
 #include "mdgemm_internal.h"
+#include "resid.h"
 #include "rule.h"
 
 #include <algorithm>
@@ -252,6 +253,9 @@ struct Scratch {
     void* owned[8] = {};
     int nowned = 0;
 
+    // whether the caller's workspace still holds this much (the pool: always)
+    bool holds(size_t bytes) const { return !user || used + (bytes + 255) / 256 * 256 <= user_bytes; }
+
     int get(size_t bytes, void** out)
     {
         bytes = (bytes + 255) / 256 * 256;
@@ -322,6 +326,18 @@ size_t small_bytes(int64_t M, int64_t N)
     return (size_t)(3 * round_up(M + 64, 64) + 3 * round_up(N + 64, 64) + 64) * sizeof(int32_t) + 7 * 256;
 }
 
+
+// Whether a product of these slices runs as residue products (resid.h), and
+// its parameters.
+bool take_residues(int form, int S, int beta, int64_t M, int64_t N, int64_t K, bool duo, ResPlan& rp, ResPanels& pn)
+{
+    // products too small for either path's arithmetic to matter (64^3
+    // double-doubles, say): without the estimate
+    if ((double)M * N * K * S * S < 1.5e8)
+        return false;
+    return res_plan(form == MD_FORM_INT8_BAL, form == MD_FORM_FP64, S, beta, K, rp) &&
+           res_pays(rp, M, N, K, duo) && res_panels(rp, M, N, K, pn);
+}
 
 // Slice parameters of a call and what the rule certified.
 struct Choice {
@@ -573,6 +589,17 @@ size_t md_gemm_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S)
                                     : (size_t)4 * ncol * 256 * sizeof(int64_t) > 160 * 1024;
     if (global)
         bytes += (size_t)gd_elements(M, N, S, is_i8(form) ? 2 : 1) * sizeof(int64_t) + 256;
+    // the residue contraction's planes where it is taken (FP64: the digit
+    // width that takes the most)
+    const int b0 = form == MD_FORM_INT8 ? 7 : 8, b1 = form == MD_FORM_FP64 ? 24 : b0;
+    for (int b = b0; b <= b1; ++b) {
+        ResPlan rp;
+        ResPanels pn;
+        if (take_residues(form, S, b, M, N, K, true, rp, pn))
+            bytes = std::max(bytes, small_bytes(M, N) + digits_bytes(MD_FORM_INT8, M, K, 1) +
+                                        digits_bytes(MD_FORM_INT8, N, K, 1) + digits_bytes(MD_FORM_INT8, M, K, rp.SB) +
+                                        digits_bytes(MD_FORM_INT8, N, K, rp.SB) + pn.bytes + 4096);
+    }
     return bytes;
 }
 
@@ -757,6 +784,58 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
     const bool global_fold = needs_global_fold(o.form, band, S, ncol);
     if ((size_t)ncol * 256 * sizeof(int64_t) > 160 * 1024)
         return MD_ERANGE;
+
+    // the residue contraction, where it pays and the scratch holds its planes
+    {
+        ResPlan rp;
+        ResPanels pn;
+        void *dA = nullptr, *dB = nullptr, *work = nullptr;
+        if (!dbg && take_residues(o.form, S, beta, M, N, K, duo, rp, pn)) {
+            const size_t bA = digits_bytes(MD_FORM_INT8, M, K, rp.SB), bB = digits_bytes(MD_FORM_INT8, N, K, rp.SB);
+            if (scr.holds(bA + bB + pn.bytes + 512) && !scr.get(bA, &dA) && !scr.get(bB, &dB) && !scr.get(pn.bytes, &work)) {
+                GemmArgs ga;
+                memset(&ga, 0, sizeof(ga));
+                ga.A = dA;
+                ga.B = dB;
+                ga.E = E;
+                ga.F = F;
+                ga.C = C;
+                ga.ldc = ldc;
+                ga.psc = plane_stride_C;
+                ga.M = M;
+                ga.N = N;
+                ga.nkc = (K + kKcI8 - 1) / kKcI8;
+                ga.S = S;
+                ga.beta = beta;
+                ga.m = m;
+                ga.ncol = ncol;
+                if (fx) {
+                    ga.fixX = fx->X;
+                    ga.fixScale = fx->scale;
+                    ga.fixNL = fx->nlimb;
+                }
+                const int64_t ra = Mp / kRowBlock, rb = Np / kRowBlock;
+                const bool bal = o.form == MD_FORM_INT8_BAL;
+                if (is_i8(o.form)) {
+                    if ((e = launch_split_i8(opA, m, E, S, ra, ga.nkc, (int8_t*)dA, nullptr, bal, st)) != hipSuccess ||
+                        (e = launch_split_i8(opB, m, F, S, rb, ga.nkc, (int8_t*)dB, nullptr, bal, st)) != hipSuccess)
+                        return hip_fail(e);
+                } else if ((e = launch_split_f64b(opA, m, E, S, beta, rp.nb, ra, ga.nkc, (int8_t*)dA, st)) != hipSuccess ||
+                           (e = launch_split_f64b(opB, m, F, S, beta, rp.nb, rb, ga.nkc, (int8_t*)dB, st)) != hipSuccess) {
+                    return hip_fail(e);
+                }
+                if (o.ev_gemm_begin && (e = hipEventRecord((hipEvent_t)o.ev_gemm_begin, st)) != hipSuccess)
+                    return hip_fail(e);
+                if ((e = launch_resid(rp, pn, ga, (char*)work, st)) != hipSuccess)
+                    return hip_fail(e);
+                if (o.ev_gemm_end && (e = hipEventRecord((hipEvent_t)o.ev_gemm_end, st)) != hipSuccess)
+                    return hip_fail(e);
+                if (o.info)
+                    fill_info(o.info, ch, T, o.validate != 0);
+                return MD_OK;
+            }
+        }
+    }
 
     const int64_t kcc = std::max<int64_t>(kc / kcg, 1);
     int64_t* fixD = nullptr;

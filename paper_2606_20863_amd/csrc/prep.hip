@@ -26,6 +26,7 @@
 // X = sum_s d_s 256^(S-1-s) with d_s in [-128, 127].  |X| < 2^(8S-2), inside
 // what S such digits reach.
 #include "mdgemm_internal.h"
+#include "resid.h"
 #include "split.h"
 #include "ldslimbs.h"
 
@@ -532,6 +533,69 @@ __global__ __launch_bounds__(256) void k_split_f64(Operand op, const int32_t* E,
     }
 }
 
+// FP64 digits as byte planes for the residue contraction: digit s (beta
+// bits, sign-magnitude words as in k_split_f64) is written as NB balanced
+// bytes, d = sum_k c_k 256^k with c_k in [-128, 127] (|d| < 2^beta fits), byte
+// k in plane s NB + k: 1 NB bytes per digit instead of 8, in the INT8
+// fragment order.  Threads, entries and stores as in k_split_i8.
+template <int MW, int EPT>
+__global__ __launch_bounds__(256) void k_split_f64b(Operand op, const int32_t* E, int S, int beta, int NB,
+                                                    int64_t nkc, int8_t* out, int64_t rb0)
+{
+    constexpr int parts = 4 / EPT;
+    typedef typename Bytes<EPT>::type Store;
+    const int64_t rb = rb0 + blockIdx.y, kc = blockIdx.x / parts;
+    const int byte0 = EPT * ((int)threadIdx.x + 256 * (int)(blockIdx.x % parts));
+    const int L = byte0 >> 4;                 // fragment lane
+    const int64_t r = rb * kRowBlock + (L & 15);
+    const int64_t kbase = kc * kKcI8 + 16 * (L >> 4) + (byte0 & 15);
+    const bool row_ok = r < op.R;
+    const int Er = row_ok ? E[r] : 0;
+    const int D = 63 / beta, W = D * beta;
+
+    uint64_t mant[EPT][MW];
+    int sh0[EPT][MW];
+    bool neg[EPT][MW];
+#pragma unroll
+    for (int q = 0; q < EPT; ++q) {
+        const int64_t k = kbase + q;
+        const bool ok = row_ok && k < op.K;
+#pragma unroll
+        for (int w = 0; w < MW; ++w) {
+            const double x = ok ? op.p[w * op.ps + r * op.sr + k * op.sk] : 0.0;
+            int ex;
+            neg[q][w] = decode(x, mant[q][w], ex);
+            sh0[q][w] = ex - Er;
+        }
+    }
+    const uint64_t wmask = (1ull << W) - 1, dmask = (1ull << beta) - 1;
+    Store* o = reinterpret_cast<Store*>(out + ((rb * nkc + kc) * (int64_t)(S * NB)) * 1024 + byte0);
+    const int nl = (S + D - 1) / D;
+    for (int j = 0; j < nl; ++j) {
+        uint64_t P[EPT], N[EPT];
+#pragma unroll
+        for (int q = 0; q < EPT; ++q)
+            limb_pair<MW>(mant[q], sh0[q], neg[q], W * (j + 1), wmask, P[q], N[q]);
+        for (int i = 0; i < D; ++i) {
+            const int s = D * j + i;
+            if (s >= S)
+                break;
+            const int rs = W - beta * (i + 1);
+            uint32_t u[EPT];
+#pragma unroll
+            for (int q = 0; q < EPT; ++q)
+                u[q] = (uint32_t)((int)((P[q] >> rs) & dmask) - (int)((N[q] >> rs) & dmask)) + 0x80808080u;
+            for (int k = 0; k < NB; ++k) {
+                uint32_t packed = 0;
+#pragma unroll
+                for (int q = 0; q < EPT; ++q)
+                    packed |= (((u[q] >> (8 * k)) & 0xffu) ^ 0x80u) << (8 * q);
+                o[(int64_t)(s * NB + k) * (1024 / EPT)] = (Store)packed;
+            }
+        }
+    }
+}
+
 }  // namespace
 
 hipError_t launch_fill_zero(double* C, int m, int64_t M, int64_t N, int64_t ldc, int64_t psc,
@@ -828,6 +892,36 @@ hipError_t launch_split_f64(const Operand& op, int m, const int32_t* E, int S, i
     case 4: return split_f64_m<4>(op, E, S, beta, nrb, nkc, out, dbg, st);
     case 8: return split_f64_m<8>(op, E, S, beta, nrb, nkc, out, dbg, st);
     case 16: return split_f64_m<16>(op, E, S, beta, nrb, nkc, out, dbg, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+template <int MW>
+hipError_t split_f64b_m(const Operand& op, const int32_t* E, int S, int beta, int nb, int64_t nrb, int64_t nkc,
+                        int8_t* out, hipStream_t st)
+{
+    constexpr int EPT = split_ept(MW);
+    if (nkc * (4 / EPT) > 0x7fffffff)
+        return hipErrorInvalidValue;
+    for (int64_t y0 = 0; y0 < nrb; y0 += kMaxGridY) {
+        const dim3 grid((unsigned)(nkc * (4 / EPT)), (unsigned)std::min<int64_t>(nrb - y0, kMaxGridY));
+        hipLaunchKernelGGL((k_split_f64b<MW, EPT>), grid, dim3(256), 0, st, op, E, S, beta, nb, nkc, out, y0);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_split_f64b(const Operand& op, int m, const int32_t* E, int S, int beta, int nb, int64_t nrb,
+                             int64_t nkc, int8_t* out, hipStream_t st)
+{
+    switch (m) {
+    case 1: return split_f64b_m<1>(op, E, S, beta, nb, nrb, nkc, out, st);
+    case 2: return split_f64b_m<2>(op, E, S, beta, nb, nrb, nkc, out, st);
+    case 4: return split_f64b_m<4>(op, E, S, beta, nb, nrb, nkc, out, st);
+    case 8: return split_f64b_m<8>(op, E, S, beta, nb, nrb, nkc, out, st);
+    case 16: return split_f64b_m<16>(op, E, S, beta, nb, nrb, nkc, out, st);
     default: return hipErrorInvalidValue;
     }
 }
