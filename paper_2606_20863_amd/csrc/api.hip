@@ -327,6 +327,56 @@ size_t small_bytes(int64_t M, int64_t N)
 }
 
 
+int fixed_limbs_of(int beta, int S, int64_t K)
+{
+    // |X| < K 2^(beta (S+1) + 1): two's complement with one bit to spare
+    return (beta * (S + 1) + ceil_log2(std::max<int64_t>(K, 1)) + 3 + 31) / 32;
+}
+
+// Depth parts of a whole-triangle INT8 product.  The kernels run one 64 x 32
+// tile of outputs per compute unit over the whole depth, so few tiles (or a
+// last round that is nearly empty) leave most of the chip idle; parts of the
+// depth, each one exactness chunk, run side by side instead, and their exact
+// integers are added and rounded by a second kernel (launch_parts_round).
+// Expected microseconds: rounds of tiles at 0.0092 us per S (S+1) and 64
+// depths plus 15 us of prologue and fold; the parts' limbs at 4 TB/s, and 6
+// us for the second launch.  (4096 x 24 x 4096 quad-doubles, 64 tiles: 442
+// us whole.)  A depth over several exactness chunks had one row block per
+// wave and a fold after each chunk, about 1.3 times the time per depth.
+struct TriParts {
+    int parts = 1, nlimb = 0;
+    int64_t per = 0;       // depth chunks of a part
+    size_t bytes = 0;      // their integers and scales (parts > 1)
+    double us = 0;
+};
+
+TriParts tri_parts(int form, int beta, int S, int64_t M, int64_t N, int64_t K)
+{
+    TriParts best;
+    const int64_t nkc = (K + kKcI8 - 1) / kKcI8;
+    const int64_t kcc = std::max<int64_t>(chunk_depth(S, digit_max(form, beta), K, (int64_t)1 << 31, kKcI8) / kKcI8, 1);
+    const double tiles = (double)((M + 63) / 64) * (double)((N + 31) / 32), step = 0.0092 * S * (S + 1);
+    best.nlimb = fixed_limbs_of(beta, S, K);
+    best.per = nkc;
+    best.us = kcc >= nkc ? std::ceil(tiles / 256) * (nkc * step + 15)
+                         : std::ceil(tiles / 128) * (nkc * step * 0.65 + 15);   // 32 x 32 tiles
+    for (int p = 2; p <= 64 && p <= nkc; ++p) {
+        const int64_t per = (nkc + p - 1) / p;
+        const int parts = (int)((nkc + per - 1) / per);
+        if (per > kcc || parts < 2)
+            continue;
+        const size_t bytes = ((size_t)best.nlimb * parts + 1) * 4 * (size_t)M * (size_t)N;
+        const double us = std::ceil(tiles * parts / 256) * (per * step + 15) + 6 + 2.0 * bytes / 4e6;
+        if (bytes <= ((size_t)1 << 30) && us < 0.95 * best.us) {
+            best.parts = parts;
+            best.per = per;
+            best.bytes = bytes;
+            best.us = us;
+        }
+    }
+    return best;
+}
+
 // Whether a product of these slices runs as residue products (resid.h), and
 // its parameters.
 bool take_residues(int form, int S, int beta, int64_t M, int64_t N, int64_t K, bool duo, ResPlan& rp, ResPanels& pn)
@@ -335,8 +385,9 @@ bool take_residues(int form, int S, int beta, int64_t M, int64_t N, int64_t K, b
     // double-doubles, say): without the estimate
     if ((double)M * N * K * S * S < 1.5e8)
         return false;
+    const double tri = is_i8(form) && S <= kTriMaxI8 ? tri_parts(form, beta, S, M, N, K).us : 0.0;
     return res_plan(form == MD_FORM_INT8_BAL, form == MD_FORM_FP64, S, beta, K, rp) &&
-           res_pays(rp, M, N, K, duo) && res_panels(rp, M, N, K, pn);
+           res_pays(rp, M, N, K, duo, tri) && res_panels(rp, M, N, K, pn);
 }
 
 // Slice parameters of a call and what the rule certified.
@@ -589,6 +640,12 @@ size_t md_gemm_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S)
                                     : (size_t)4 * ncol * 256 * sizeof(int64_t) > 160 * 1024;
     if (global)
         bytes += (size_t)gd_elements(M, N, S, is_i8(form) ? 2 : 1) * sizeof(int64_t) + 256;
+    // the depth parts' integers
+    if (is_i8(form) && S <= kTriMaxI8 && K > 0) {
+        const TriParts tp = tri_parts(form, form == MD_FORM_INT8 ? 7 : 8, S, M, N, K);
+        if (tp.parts > 1)
+            bytes += tp.bytes + 256;
+    }
     // the residue contraction's planes where it is taken (FP64: the digit
     // width that takes the most)
     const int b0 = form == MD_FORM_INT8 ? 7 : 8, b1 = form == MD_FORM_FP64 ? 24 : b0;
@@ -860,6 +917,17 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
         }
     }
 
+    // depth parts of the whole triangle, where the scratch holds their integers
+    TriParts tp;
+    int32_t* partX = nullptr;
+    if (!fx && !dbg && is_i8(o.form) && band == S && S <= kTriMaxI8) {
+        tp = tri_parts(o.form, beta, S, M, N, K);
+        void* p = nullptr;
+        const size_t dig = digits_bytes(o.form, M, K, S) + digits_bytes(o.form, N, K, S);
+        if (tp.parts > 1 && scr.holds(dig + tp.bytes + 256) && !scr.get(tp.bytes, &p))
+            partX = (int32_t*)p;
+    }
+
     void *dA, *dB;
     int rc = scr.get(digits_bytes(o.form, M, K, S), &dA);
     if (rc)
@@ -920,10 +988,19 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
     ga.fixX = fx && !fixD ? fx->X : nullptr;
     ga.fixScale = fx && !fixD ? fx->scale : nullptr;
     ga.fixNL = fx ? fx->nlimb : 0;
+    if (partX) {
+        ga.kcc = tp.per;
+        ga.fixX = partX;
+        ga.fixNL = tp.nlimb;
+        ga.fixScale = partX + (int64_t)tp.parts * tp.nlimb * M * N;
+    }
     if (o.ev_gemm_begin && (e = hipEventRecord((hipEvent_t)o.ev_gemm_begin, st)) != hipSuccess)
         return hip_fail(e);
     e = is_i8(o.form) ? launch_gemm_i8(ga, st) : launch_gemm_f64(ga, st);
     if (e != hipSuccess)
+        return hip_fail(e);
+    if (partX && (e = launch_parts_round(m, M, N, tp.nlimb, tp.parts, partX, ga.fixScale, C, ldc, plane_stride_C, st)) !=
+                     hipSuccess)
         return hip_fail(e);
     if (global_fold && (e = launch_gemm_final(ga, st)) != hipSuccess)
         return hip_fail(e);
@@ -1279,8 +1356,7 @@ int md_fixed_limbs(int beta, int S, int64_t K)
 {
     if (beta < 1 || beta > 24 || S < 1 || S > 512 || K < 0)
         return -1;
-    // |X| < K 2^(beta (S+1) + 1): two's complement with one bit to spare
-    return (beta * (S + 1) + ceil_log2(std::max<int64_t>(K, 1)) + 3 + 31) / 32;
+    return fixed_limbs_of(beta, S, K);
 }
 
 int md_exponents(int64_t M, int64_t N, int64_t K, const double* A, int64_t lda, const double* B,

@@ -94,6 +94,45 @@ __global__ __launch_bounds__(256) void k_fixed_round(int m, int64_t count, int n
         C[w * psc + e] = rn_next(L, sgn, sc);
 }
 
+// C = the sum of a product's depth parts (each nlimb limb planes of M N
+// entries), rounded: one carry chain over the parts' limbs per entry, then
+// the greedy rounding.  Bound by the reads, 4 parts nlimb bytes per entry.
+template <int NL>
+__global__ __launch_bounds__(256) void k_parts_round(int m, int64_t M, int64_t N, int nlimb, int parts,
+                                                     const int32_t* X, const int32_t* scale, double* C,
+                                                     int64_t ldc, int64_t psc)
+{
+    const int64_t count = M * N;
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= count)
+        return;
+    uint32_t L[NL];
+    int64_t cy = 0;   // the limbs' unsigned sums; every part's top limb is signed
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        if (k < nlimb)
+            for (int p = 0; p < parts; ++p) {
+                const int32_t v = X[((int64_t)p * nlimb + k) * count + e];
+                cy += k == nlimb - 1 ? (int64_t)v : (int64_t)(uint32_t)v;
+            }
+        L[k] = (uint32_t)cy;
+        cy >>= 32;
+    }
+    const bool neg = cy < 0 || (int32_t)L[NL - 1] < 0;
+    uint64_t up = 1;
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const uint64_t v = (uint64_t)(~L[k]) + up;
+        up = v >> 32;
+        L[k] = neg ? (uint32_t)v : L[k];
+    }
+    double sgn = neg ? -1.0 : 1.0;
+    int sc = scale[e];
+    double* out = C + e / N * ldc + e % N;
+    for (int w = 0; w < m; ++w)
+        out[w * psc] = rn_next(L, sgn, sc);
+}
+
 unsigned blocks_of(int64_t count) { return (unsigned)((count + 255) / 256); }
 
 template <int NL>
@@ -156,6 +195,23 @@ hipError_t launch_fixed_round(int m, int64_t count, int nlimb, const int32_t* X,
     if (nlimb <= 48) return round_nl<48>(m, count, nlimb, X, scale, C, psc, st);
     if (nlimb <= 80) return round_nl<80>(m, count, nlimb, X, scale, C, psc, st);
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_parts_round(int m, int64_t M, int64_t N, int nlimb, int parts, const int32_t* X,
+                              const int32_t* scale, double* C, int64_t ldc, int64_t psc, hipStream_t st)
+{
+    if ((M * N + 255) / 256 > 0x7fffffff)
+        return hipErrorInvalidValue;
+    const dim3 grid(blocks_of(M * N));
+    if (nlimb <= 4)
+        hipLaunchKernelGGL(k_parts_round<4>, grid, dim3(256), 0, st, m, M, N, nlimb, parts, X, scale, C, ldc, psc);
+    else if (nlimb <= 8)
+        hipLaunchKernelGGL(k_parts_round<8>, grid, dim3(256), 0, st, m, M, N, nlimb, parts, X, scale, C, ldc, psc);
+    else if (nlimb <= 12)
+        hipLaunchKernelGGL(k_parts_round<12>, grid, dim3(256), 0, st, m, M, N, nlimb, parts, X, scale, C, ldc, psc);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 }  // namespace mdg

@@ -265,6 +265,9 @@ hipError_t launch_fixed_from_D(const int64_t* D, int S, int beta, int64_t M, int
 // Z = X + Y mod 2^(32 nlimb), limb planes of count entries
 hipError_t launch_fixed_add(int64_t count, int nlimb, const int32_t* X, const int32_t* Y, int32_t* Z,
                             hipStream_t st);
+// C = round(sum of the depth parts' integers, X [parts][nlimb][M N]); nlimb <= 12
+hipError_t launch_parts_round(int m, int64_t M, int64_t N, int nlimb, int parts, const int32_t* X,
+                              const int32_t* scale, double* C, int64_t ldc, int64_t psc, hipStream_t st);
 // greedy round to nearest of X 2^scale into m words (plane stride psc)
 hipError_t launch_fixed_round(int m, int64_t count, int nlimb, const int32_t* X, const int32_t* scale,
                               double* C, int64_t psc, hipStream_t st);

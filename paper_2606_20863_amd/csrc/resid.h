@@ -57,8 +57,9 @@ bool res_plan(bool balanced, bool fp64, int S, int beta, int64_t K, ResPlan& r);
 int res_limbs(const ResPlan& r, int64_t K);
 
 // Whether it is expected to be faster than the form's slice products (duo:
-// the call may take the two-band INT8 kernel).
-bool res_pays(const ResPlan& r, int64_t M, int64_t N, int64_t K, bool duo);
+// the call may take the two-band INT8 kernel; tri_us: what the whole-triangle
+// INT8 kernels are expected to take, where they apply, else 0).
+bool res_pays(const ResPlan& r, int64_t M, int64_t N, int64_t K, bool duo, double tri_us);
 
 // Scratch of one panel (Mr x Nc outputs, depth K) and the panel sizes that
 // keep it below the limit; false if none does.

@@ -949,9 +949,9 @@ bool res_plan(bool balanced, bool fp64, int S, int beta, int64_t K, ResPlan& r)
 // So FP64 digits change over at about 512^3 double-doubles (126 us against
 // 100) and below 128^3 quad-doubles (115 against 90); INT8 octo-doubles at
 // about 256^3 (181 against 168), hexa-doubles at 128^3, quad-doubles at
-// about 2048^3 (2129 against 1993; 4096^3: 15.9 ms against 12.4) or where the depth is
-// long (256 x 256 x 4096: 444 against 267), double-doubles never.
-bool res_pays(const ResPlan& r, int64_t M, int64_t N, int64_t K, bool duo)
+// about 2048^3 (2129 against 1993; 4096^3: 15.9 ms against 12.4), double-
+// doubles never.
+bool res_pays(const ResPlan& r, int64_t M, int64_t N, int64_t K, bool duo, double tri_us)
 {
     const double dM = (double)M, dN = (double)N, dK = (double)K, dS = r.S;
     const double steps = (double)res_steps(K), planes = r.planes();
@@ -964,8 +964,10 @@ bool res_pays(const ResPlan& r, int64_t M, int64_t N, int64_t K, bool duo)
     double slices;
     if (r.nb) {
         slices = 40 + std::max(dM * dN * dK * dS * (dS + 1) / 62e6, 0.0045 * dK * dS * (dS + 1));
+    } else if (tri_us > 0) {
+        slices = 30 + tri_us;
     } else {
-        const double per = r.S <= kTriMaxI8 ? 0.0092 : duo && r.S <= kDuoMax ? 0.0113 : 0.0134;
+        const double per = duo && r.S <= kDuoMax ? 0.0113 : 0.0134;
         slices = 30 + std::ceil(std::ceil(dM / 64) * std::ceil(dN / 32) / 256) *
                           (std::ceil(dK / 64) * dS * (dS + 1) * per + 15);
     }

@@ -253,7 +253,9 @@ __global__ __launch_bounds__(256, 1) void k_tri2_i8(GemmArgs a)
 
 // The same contraction returning the exact integers (a.fixX, a.fixScale)
 // instead of rounded words.  (Its own copy of the body: the rounding
-// kernel's code stays exactly as it is tuned.)
+// kernel's code stays exactly as it is tuned.)  Workgroups of grid row y
+// take the depth chunks [y kcc, (y+1) kcc) and write the integer of that
+// part, a.fixNL limb planes each (their sum is the product's integer).
 template <int S, int B>
 __global__ __launch_bounds__(256, 1) void k_tri2_i8_fixed(GemmArgs a)
 {
@@ -266,13 +268,14 @@ __global__ __launch_bounds__(256, 1) void k_tri2_i8_fixed(GemmArgs a)
         LA[r] = frag_stream((const char*)a.A + (w.rb + r) * bytes, w.rb + r < nrb ? bytes : 0,
                             w.lane);
     const FragStream LB = frag_stream((const char*)a.B + w.cb * bytes, bytes, w.lane);
+    const int64_t part = blockIdx.y, c0 = part * a.kcc;
     v4i acc[2][S];
 #pragma unroll
     for (int r = 0; r < 2; ++r)
 #pragma unroll
         for (int g = 0; g < S; ++g)
             acc[r][g] = FormI8::zero();
-    tri_run_i8<S, 2, kLeadA>(acc, LA, LB, 0, a.nkc);
+    tri_run_i8<S, 2, kLeadA>(acc, LA, LB, c0, min(c0 + a.kcc, a.nkc));
     int64_t x[8][Tri<S, B>::kCols];
 #pragma unroll
     for (int n = 0; n < 8; ++n)
@@ -280,6 +283,7 @@ __global__ __launch_bounds__(256, 1) void k_tri2_i8_fixed(GemmArgs a)
         for (int j = 0; j < Tri<S, B>::kCols; ++j)
             x[n][j] = 0;
     tri_fold<S, 2, false, B>(acc, x, a, w.rb, w.cb, w.lane);
+    a.fixX += part * a.fixNL * a.M * a.N;
     tri_outputs<S, 2, B, true>(x, a, w.rb, w.cb, w.lane);
 }
 
@@ -302,16 +306,22 @@ struct DispatchTriRange {
     }
 };
 
-// The fixed-point variant for a.S in [LO, S]: the whole depth must be one
-// exactness chunk.
+// The fixed-point variant for a.S in [LO, S]: every part of a.kcc depth
+// chunks must be one exactness chunk (the caller's choice of kcc).
 template <int S, int LO, int B>
 struct DispatchTriFixRange {
     static hipError_t run(const GemmArgs& a, hipStream_t st)
     {
-        if (a.kcc < a.nkc || !a.fixX || !a.fixScale)
+        if (a.kcc < 1 || !a.fixX || !a.fixScale)
             return hipErrorInvalidValue;
-        if (a.S == S)
-            return launch_kernel(k_tri2_i8_fixed<S, B>, a, st, false, 2 * kTile);
+        if (a.S == S) {
+            const int64_t tiles = ((a.N + kTile - 1) / kTile) * ((a.M + 2 * kTile - 1) / (2 * kTile));
+            const int64_t parts = (a.nkc + a.kcc - 1) / a.kcc;
+            if (parts > 65535)
+                return hipErrorInvalidValue;
+            hipLaunchKernelGGL((k_tri2_i8_fixed<S, B>), dim3((unsigned)tiles, (unsigned)parts), dim3(256), 0, st, a);
+            return hipGetLastError();
+        }
         if constexpr (S > LO)
             return DispatchTriFixRange<S - 1, LO, B>::run(a, st);
         return hipErrorInvalidValue;
