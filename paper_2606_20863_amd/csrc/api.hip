@@ -798,12 +798,16 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
                round_up(M, kTile) / kRowBlock, nullptr};
     ExpSide sb{opB, hiB, loB, F, dbg ? dbg->F : nullptr, stats + 1, stats + 6, (opB.sr == 1 && opB.sk != 1) ? 1 : 0,
                round_up(N, kTile) / kRowBlock, nullptr};
-    if ((e = launch_exp_pass2(sa, sb, stats, eoff, st)) != hipSuccess)
+    // the exponent pass: one launch where the depth is short and the
+    // magnitude split follows (which then makes the statistics) or nobody
+    // reads them
+    const bool use_rho = o.force_S == 0 && o.s_rule == MD_S_RHO;
+    const bool exp_rows = K <= kExpRowsDepth && (use_rho || o.force_S > 0);
+    if ((e = exp_rows ? launch_exp_rows2(sa, sb, eoff, st) : launch_exp_pass2(sa, sb, stats, eoff, st)) != hipSuccess)
         return hip_fail(e);
     if (E_in && (e = launch_exp_set(E_in, hiA, M, eoff, E, exp_flags, st)) != hipSuccess) return hip_fail(e);
     if (F_in && (e = launch_exp_set(F_in, hiB, N, eoff, F, exp_flags, st)) != hipSuccess) return hip_fail(e);
 
-    const bool use_rho = o.force_S == 0 && o.s_rule == MD_S_RHO;
     if (use_rho) {
         // magnitude certificate: min_ij sum_k qA_ik qB_kj, q the 7-bit
         // leading-word magnitudes on the shared-exponent grid
@@ -817,7 +821,8 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
             return rc;
         sa.q = (int8_t*)qA;
         sb.q = (int8_t*)qB;
-        if ((e = launch_split_mag2(sa, sb, eoff, nkm, st)) != hipSuccess)
+        if ((e = launch_split_mag2(sa, sb, eoff, nkm, st,
+                                   exp_rows ? (unsigned long long*)(stats + 2) : nullptr)) != hipSuccess)
             return hip_fail(e);
         if ((e = launch_mag_min(qA, qB, M, N, nkm, (unsigned long long*)(stats + 2), st)) != hipSuccess)
             return hip_fail(e);
@@ -871,16 +876,11 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
                     ga.fixScale = fx->scale;
                     ga.fixNL = fx->nlimb;
                 }
-                const int64_t ra = Mp / kRowBlock, rb = Np / kRowBlock;
-                const bool bal = o.form == MD_FORM_INT8_BAL;
-                if (is_i8(o.form)) {
-                    if ((e = launch_split_i8(opA, m, E, S, ra, ga.nkc, (int8_t*)dA, nullptr, bal, st)) != hipSuccess ||
-                        (e = launch_split_i8(opB, m, F, S, rb, ga.nkc, (int8_t*)dB, nullptr, bal, st)) != hipSuccess)
-                        return hip_fail(e);
-                } else if ((e = launch_split_f64b(opA, m, E, S, beta, rp.nb, ra, ga.nkc, (int8_t*)dA, st)) != hipSuccess ||
-                           (e = launch_split_f64b(opB, m, F, S, beta, rp.nb, rb, ga.nkc, (int8_t*)dB, st)) != hipSuccess) {
+                const SplitSide pa{opA, E, Mp / kRowBlock, dA, nullptr}, pb{opB, F, Np / kRowBlock, dB, nullptr};
+                e = is_i8(o.form) ? launch_split_i8(pa, pb, m, S, ga.nkc, o.form == MD_FORM_INT8_BAL, st)
+                                  : launch_split_f64b(pa, pb, m, S, beta, rp.nb, ga.nkc, st);
+                if (e != hipSuccess)
                     return hip_fail(e);
-                }
                 if (o.ev_gemm_begin && (e = hipEventRecord((hipEvent_t)o.ev_gemm_begin, st)) != hipSuccess)
                     return hip_fail(e);
                 if ((e = launch_resid(rp, pn, ga, (char*)work, st)) != hipSuccess)
@@ -936,16 +936,12 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
     if (rc)
         return rc;
 
-    if (is_i8(o.form)) {
-        const bool bal = o.form == MD_FORM_INT8_BAL;
-        if ((e = launch_split_i8(opA, m, E, S, Mp / kRowBlock, nkc, (int8_t*)dA, dbg ? dbg->digits_A : nullptr, bal, st)) != hipSuccess)
-            return hip_fail(e);
-        if ((e = launch_split_i8(opB, m, F, S, Np / kRowBlock, nkc, (int8_t*)dB, dbg ? dbg->digits_B : nullptr, bal, st)) != hipSuccess)
-            return hip_fail(e);
-    } else {
-        if ((e = launch_split_f64(opA, m, E, S, beta, Mp / kRowBlock, nkc, (double*)dA, dbg ? dbg->digits_A : nullptr, st)) != hipSuccess)
-            return hip_fail(e);
-        if ((e = launch_split_f64(opB, m, F, S, beta, Np / kRowBlock, nkc, (double*)dB, dbg ? dbg->digits_B : nullptr, st)) != hipSuccess)
+    {
+        const SplitSide pa{opA, E, Mp / kRowBlock, dA, dbg ? dbg->digits_A : nullptr};
+        const SplitSide pb{opB, F, Np / kRowBlock, dB, dbg ? dbg->digits_B : nullptr};
+        e = is_i8(o.form) ? launch_split_i8(pa, pb, m, S, nkc, o.form == MD_FORM_INT8_BAL, st)
+                          : launch_split_f64(pa, pb, m, S, beta, nkc, st);
+        if (e != hipSuccess)
             return hip_fail(e);
     }
     if (dbg && dbg->D) {
@@ -1248,18 +1244,11 @@ int md_dot_ex(int m, int64_t batch, int64_t n, const double* X, int64_t ldx, int
         rc = scr.get(digits_bytes(o.form, batch, n, S), &dY);
         if (rc)
             return rc;
-        if (is_i8(o.form)) {
-            const bool bal = o.form == MD_FORM_INT8_BAL;
-            if ((e = launch_split_i8(opX, m, E, S, nrb, nkc, (int8_t*)dX, nullptr, bal, st)) != hipSuccess)
-                return hip_fail(e);
-            if ((e = launch_split_i8(opY, m, F, S, nrb, nkc, (int8_t*)dY, nullptr, bal, st)) != hipSuccess)
-                return hip_fail(e);
-        } else {
-            if ((e = launch_split_f64(opX, m, E, S, beta, nrb, nkc, (double*)dX, nullptr, st)) != hipSuccess)
-                return hip_fail(e);
-            if ((e = launch_split_f64(opY, m, F, S, beta, nrb, nkc, (double*)dY, nullptr, st)) != hipSuccess)
-                return hip_fail(e);
-        }
+        const SplitSide px{opX, E, nrb, dX, nullptr}, py{opY, F, nrb, dY, nullptr};
+        e = is_i8(o.form) ? launch_split_i8(px, py, m, S, nkc, o.form == MD_FORM_INT8_BAL, st)
+                          : launch_split_f64(px, py, m, S, beta, nkc, st);
+        if (e != hipSuccess)
+            return hip_fail(e);
         if ((e = launch_fill_zero_i64((int64_t*)Dp, (int64_t)S * batch, st)) != hipSuccess)
             return hip_fail(e);
 

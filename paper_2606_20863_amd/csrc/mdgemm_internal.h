@@ -119,7 +119,17 @@ struct ExpSide {
     int8_t* q;               // magnitude digits
 };
 hipError_t launch_exp_pass2(const ExpSide& a, const ExpSide& b, int32_t* stats, int eoff, hipStream_t st);
-hipError_t launch_split_mag2(const ExpSide& a, const ExpSide& b, int eoff, int64_t nkc, hipStream_t st);
+hipError_t launch_split_mag2(const ExpSide& a, const ExpSide& b, int eoff, int64_t nkc, hipStream_t st,
+                             unsigned long long* minP = nullptr);
+// The exponent pass in one launch (a block takes its rows' whole depth: K up
+// to kExpRowsDepth), E and hi as launch_exp_pass2's.  It leaves no
+// statistics: launch_split_mag2 with minP makes them (a call that needs
+// none, with S forced, stops here).  lo is its working space.  A thread
+// reads K / 16 words one batch after the other: at K = 1024 the block's
+// chain of loads costs more than the two launches (1024^3: 346 -> 359 us a
+// call), at 64 they are most of the pass (64^3: see launch_split_i8).
+constexpr int64_t kExpRowsDepth = 256;
+hipError_t launch_exp_rows2(const ExpSide& a, const ExpSide& b, int eoff, hipStream_t st);
 // E[r] = shared exponent + eoff (2 for the balanced INT8 digits, else 0);
 // dbgE gets the shared exponent itself; ext (optional) the largest and
 // smallest shared exponent of the rows with a nonzero leading word
@@ -142,15 +152,22 @@ hipError_t launch_cert(const int32_t* stats, int form, int64_t K, int T, int m, 
 hipError_t launch_exp_set(const int32_t* Ein, const int32_t* hi, int64_t R, int eoff, int32_t* E,
                           int32_t* flags, hipStream_t st);
 
-// INT8 digits: 7-bit sign-magnitude, or balanced 8-bit (E then holds the
+// Splits of both operands of a product.  INT8 digits: 7-bit sign-magnitude, or balanced 8-bit (E then holds the
 // shared exponent + 2)
-hipError_t launch_split_i8(const Operand& op, int m, const int32_t* E, int S, int64_t nrb,
-                           int64_t nkc, int8_t* out, int32_t* dbg, bool balanced, hipStream_t st);
+struct SplitSide {
+    Operand op;
+    const int32_t* E;     // grid exponents
+    int64_t nrb;          // 16-row blocks written
+    void* out;            // digit fragments
+    int32_t* dbg;         // optional dump of the digits
+};
+hipError_t launch_split_i8(const SplitSide& a, const SplitSide& b, int m, int S, int64_t nkc, bool balanced,
+                           hipStream_t st);
 // OR of the input-precondition flags of every entry of op into *flags
 // (1 not finite, 2 not weakly nonoverlapping, 4 leading word out of range)
 hipError_t launch_validate(const Operand& op, int m, int32_t* flags, hipStream_t st);
-hipError_t launch_split_f64(const Operand& op, int m, const int32_t* E, int S, int beta,
-                            int64_t nrb, int64_t nkc, double* out, int32_t* dbg, hipStream_t st);
+hipError_t launch_split_f64(const SplitSide& a, const SplitSide& b, int m, int S, int beta, int64_t nkc,
+                            hipStream_t st);
 
 hipError_t launch_gemm_i8(const GemmArgs& a, hipStream_t st);
 // minP[0] = min over (i < M, j < N) of sum_k qA_ik qB_kj (must start at

@@ -226,12 +226,19 @@ template <> struct Bytes<1> { typedef uint8_t type; };
 // With more words per entry, fewer entries per thread keep the decoded words
 // in registers.
 template <int MW, int EPT, bool DBG>
-__global__ __launch_bounds__(256) void k_split_i8(Operand op, const int32_t* E, int S,
-                                                  int64_t nkc, int8_t* out, int32_t* dbg, int64_t rb0)
+__global__ __launch_bounds__(256) void k_split_i8(SplitSide sa, SplitSide sb, int S, int64_t nkc, int64_t rb0)
 {
+    const SplitSide sd = blockIdx.z == 0 ? sa : sb;
+    const int64_t rb = rb0 + blockIdx.y;
+    if (rb >= sd.nrb)
+        return;
+    const Operand op = sd.op;
+    const int32_t* E = sd.E;
+    int8_t* out = (int8_t*)sd.out;
+    int32_t* dbg = sd.dbg;
     constexpr int beta = 7, D = 9, W = 63, parts = 4 / EPT;
     typedef typename Bytes<EPT>::type Store;
-    const int64_t rb = rb0 + blockIdx.y, kc = blockIdx.x / parts;
+    const int64_t kc = blockIdx.x / parts;
     const int byte0 = EPT * ((int)threadIdx.x + 256 * (int)(blockIdx.x % parts));
     const int L = byte0 >> 4;                 // fragment lane
     const int64_t r = rb * kRowBlock + (L & 15);
@@ -295,13 +302,20 @@ __global__ __launch_bounds__(256) void k_split_i8(Operand op, const int32_t* E, 
 // flipped, is the digit 128 below it, d_(S - 7 j - 1 - i), and U >> 56 (in
 // {-1, 0, 1}) is carried up.
 template <int MW, int EPT, bool DBG>
-__global__ __launch_bounds__(256) void k_split_i8bal(Operand op, const int32_t* E, int S,
-                                                     int64_t nkc, int8_t* out, int32_t* dbg, int64_t rb0)
+__global__ __launch_bounds__(256) void k_split_i8bal(SplitSide sa, SplitSide sb, int S, int64_t nkc, int64_t rb0)
 {
+    const SplitSide sd = blockIdx.z == 0 ? sa : sb;
+    const int64_t rb = rb0 + blockIdx.y;
+    if (rb >= sd.nrb)
+        return;
+    const Operand op = sd.op;
+    const int32_t* E = sd.E;
+    int8_t* out = (int8_t*)sd.out;
+    int32_t* dbg = sd.dbg;
     constexpr int D = 7, W = 56, parts = 4 / EPT;
     constexpr int64_t kBias = 0x80808080808080LL;
     typedef typename Bytes<EPT>::type Store;
-    const int64_t rb = rb0 + blockIdx.y, kc = blockIdx.x / parts;
+    const int64_t kc = blockIdx.x / parts;
     const int byte0 = EPT * ((int)threadIdx.x + 256 * (int)(blockIdx.x % parts));
     const int L = byte0 >> 4;                 // fragment lane
     const int64_t r = rb * kRowBlock + (L & 15);
@@ -430,8 +444,117 @@ __global__ void k_exp_final2(ExpSide a, ExpSide b, int eoff)
         exp_final_rows(b.hi, b.lo, b.op.R, b.E, b.span_max, b.ext, b.dbgE, eoff, r);
 }
 
-__global__ __launch_bounds__(256) void k_split_mag2(ExpSide a, ExpSide b, int eoff, int64_t nkc, int64_t rb0)
+// The whole exponent pass of both operands where the depth is short: a block
+// finds its 16 rows' exponents itself (no atomics, so no initial values and
+// no last pass: one launch instead of three), and leaves its span and
+// extreme exponents in lo[4 bx ..], which k_split_mag2 reduces.  Thread
+// (row, k) as in exp_partial_block.
+__global__ __launch_bounds__(256) void k_exp_rows2(ExpSide a, ExpSide b, int eoff)
 {
+    const ExpSide s = blockIdx.z == 0 ? a : b;
+    const int64_t r0 = (int64_t)blockIdx.x * kExpRows;
+    if (r0 >= s.op.R)
+        return;
+    __shared__ int sh[4][kExpRows], sl[4][kExpRows];
+    const int t = threadIdx.x, wave = t >> 6;
+    const int tr = s.rows_fast ? (t & 15) : (t >> 4);
+    const int tk = s.rows_fast ? (t >> 4) : (t & 15);
+    const int64_t r = r0 + tr;
+    int h = INT_MIN, l = INT_MAX;
+    if (r < s.op.R) {
+        const double* p = s.op.p + r * s.op.sr;
+#pragma unroll 16
+        for (int64_t k = tk; k < s.op.K; k += 16) {
+            const double x = p[k * s.op.sk];
+            if (x != 0.0) {
+                const int e = frexp_exponent(x);
+                h = max(h, e);
+                l = min(l, e);
+            }
+        }
+    }
+    // rows in lanes 16 apart of every wave, or in 16 adjacent lanes of one
+    for (int o = s.rows_fast ? 16 : 1; o < (s.rows_fast ? 64 : 16); o <<= 1) {
+        h = max(h, __shfl_xor(h, o));
+        l = min(l, __shfl_xor(l, o));
+    }
+    if (s.rows_fast) {
+        if ((t & 63) < 16) {
+            sh[wave][tr] = h;
+            sl[wave][tr] = l;
+        }
+    } else if (tk == 0) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            sh[w][tr] = h;
+            sl[w][tr] = l;
+        }
+    }
+    __syncthreads();
+    if (t >= kExpRows)
+        return;
+    h = max(max(sh[0][t], sh[1][t]), max(sh[2][t], sh[3][t]));
+    l = min(min(sl[0][t], sl[1][t]), min(sl[2][t], sl[3][t]));
+    const int e = h == INT_MIN ? 0 : h;
+    int span = h == INT_MIN ? 0 : h - l, emax = h, emin = h == INT_MIN ? INT_MAX : h;
+    if (r0 + t < s.op.R) {
+        s.hi[r0 + t] = h;
+        s.E[r0 + t] = e + eoff;
+        if (s.dbgE)
+            s.dbgE[r0 + t] = e;
+    }
+    for (int o = 1; o < 16; o <<= 1) {
+        span = max(span, __shfl_xor(span, o));
+        emax = max(emax, __shfl_xor(emax, o));
+        emin = min(emin, __shfl_xor(emin, o));
+    }
+    if (t == 0) {
+        int32_t* q = s.lo + 4 * (int64_t)blockIdx.x;
+        q[0] = span;
+        q[1] = emax;
+        q[2] = emin;
+    }
+}
+
+// The statistics of one side from k_exp_rows2's blocks.
+__device__ __forceinline__ void exp_rows_stats(const ExpSide& s)
+{
+    __shared__ int red[3][4];
+    const int64_t n = (s.op.R + kExpRows - 1) / kExpRows;
+    int span = 0, emax = INT_MIN, emin = INT_MAX;
+    for (int64_t b = threadIdx.x; b < n; b += 256) {
+        span = max(span, s.lo[4 * b]);
+        emax = max(emax, s.lo[4 * b + 1]);
+        emin = min(emin, s.lo[4 * b + 2]);
+    }
+    for (int o = 1; o < 64; o <<= 1) {
+        span = max(span, __shfl_xor(span, o));
+        emax = max(emax, __shfl_xor(emax, o));
+        emin = min(emin, __shfl_xor(emin, o));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = span;
+        red[1][threadIdx.x >> 6] = emax;
+        red[2][threadIdx.x >> 6] = emin;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        *s.span_max = max(max(red[0][0], red[0][1]), max(red[0][2], red[0][3]));
+        s.ext[0] = max(max(red[1][0], red[1][1]), max(red[1][2], red[1][3]));
+        s.ext[1] = min(min(red[2][0], red[2][1]), min(red[2][2], red[2][3]));
+    }
+}
+
+// minP (after k_exp_rows2, else null): the smallest magnitude product's
+// initial value, and the statistics, set here
+__global__ __launch_bounds__(256) void k_split_mag2(ExpSide a, ExpSide b, int eoff, int64_t nkc, int64_t rb0,
+                                                    unsigned long long* minP)
+{
+    if (minP && blockIdx.x == 0 && blockIdx.y == 0 && rb0 == 0) {
+        exp_rows_stats(blockIdx.z == 0 ? a : b);
+        if (blockIdx.z == 0 && threadIdx.x == 0)
+            *minP = ~0ull;
+    }
     const int64_t rb = rb0 + blockIdx.y;
     if (blockIdx.z == 0) {
         if (rb < a.nrb)
@@ -470,10 +593,14 @@ __device__ __forceinline__ double pack_doubles<1>(const double (&v)[1])
 // consecutive doubles per thread: thread u of a fragment covers doubles
 // [EPT u, EPT u + EPT), i.e. lane EPT u / 4, q from (EPT u) % 4.
 template <int MW, int EPT, bool DBG>
-__global__ __launch_bounds__(256) void k_split_f64(Operand op, const int32_t* E, int S, int beta,
-                                                   int64_t nrb, int64_t nkc, double* out,
-                                                   int32_t* dbg)
+__global__ __launch_bounds__(256) void k_split_f64(SplitSide sa, SplitSide sb, int S, int beta, int64_t nkc)
 {
+    const SplitSide sd = blockIdx.z == 0 ? sa : sb;
+    const Operand op = sd.op;
+    const int32_t* E = sd.E;
+    const int64_t nrb = sd.nrb;
+    double* out = (double*)sd.out;
+    int32_t* dbg = sd.dbg;
     constexpr int TPF = 256 / EPT;            // threads per fragment
     typedef typename Doubles<EPT>::type Store;
     const int u = threadIdx.x % TPF;
@@ -539,12 +666,19 @@ __global__ __launch_bounds__(256) void k_split_f64(Operand op, const int32_t* E,
 // k in plane s NB + k: 1 NB bytes per digit instead of 8, in the INT8
 // fragment order.  Threads, entries and stores as in k_split_i8.
 template <int MW, int EPT>
-__global__ __launch_bounds__(256) void k_split_f64b(Operand op, const int32_t* E, int S, int beta, int NB,
-                                                    int64_t nkc, int8_t* out, int64_t rb0)
+__global__ __launch_bounds__(256) void k_split_f64b(SplitSide sa, SplitSide sb, int S, int beta, int NB,
+                                                    int64_t nkc, int64_t rb0)
 {
+    const SplitSide sd = blockIdx.z == 0 ? sa : sb;
+    const int64_t rb = rb0 + blockIdx.y;
+    if (rb >= sd.nrb)
+        return;
+    const Operand op = sd.op;
+    const int32_t* E = sd.E;
+    int8_t* out = (int8_t*)sd.out;
     constexpr int parts = 4 / EPT;
     typedef typename Bytes<EPT>::type Store;
-    const int64_t rb = rb0 + blockIdx.y, kc = blockIdx.x / parts;
+    const int64_t kc = blockIdx.x / parts;
     const int byte0 = EPT * ((int)threadIdx.x + 256 * (int)(blockIdx.x % parts));
     const int L = byte0 >> 4;                 // fragment lane
     const int64_t r = rb * kRowBlock + (L & 15);
@@ -665,14 +799,24 @@ hipError_t launch_exp_pass2(const ExpSide& a, const ExpSide& b, int32_t* stats, 
     return hipGetLastError();
 }
 
-hipError_t launch_split_mag2(const ExpSide& a, const ExpSide& b, int eoff, int64_t nkc, hipStream_t st)
+hipError_t launch_exp_rows2(const ExpSide& a, const ExpSide& b, int eoff, hipStream_t st)
+{
+    const int64_t gx = (std::max(a.op.R, b.op.R) + kExpRows - 1) / kExpRows;
+    if (gx < 1 || gx > 0x7fffffff)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_exp_rows2, dim3((unsigned)gx, 1, 2), dim3(256), 0, st, a, b, eoff);
+    return hipGetLastError();
+}
+
+hipError_t launch_split_mag2(const ExpSide& a, const ExpSide& b, int eoff, int64_t nkc, hipStream_t st,
+                             unsigned long long* minP)
 {
     if (nkc > 0x7fffffff)
         return hipErrorInvalidValue;
     const int64_t nrb = std::max(a.nrb, b.nrb);
     for (int64_t y0 = 0; y0 < nrb; y0 += kMaxGridY) {
         const dim3 grid((unsigned)nkc, (unsigned)std::min<int64_t>(nrb - y0, kMaxGridY), 2);
-        hipLaunchKernelGGL(k_split_mag2, grid, dim3(256), 0, st, a, b, eoff, nkc, y0);
+        hipLaunchKernelGGL(k_split_mag2, grid, dim3(256), 0, st, a, b, eoff, nkc, y0, minP);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
@@ -721,14 +865,21 @@ hipError_t launch_exp_set(const int32_t* Ein, const int32_t* hi, int64_t R, int 
 // entry.  Digits in a container of SC >= S (the low SC - S zero); digit s
 // of the entry is container digit s, most significant first.
 template <int MW, int SC, bool BAL, bool DBG>
-__global__ __launch_bounds__(256) void k_split_place(Operand op, const int32_t* E, int S, int64_t nkc,
-                                                     int8_t* out, int32_t* dbg, int64_t rb0)
+__global__ __launch_bounds__(256) void k_split_place(SplitSide sa, SplitSide sb, int S, int64_t nkc, int64_t rb0)
 {
+    const SplitSide sd = blockIdx.z == 0 ? sa : sb;
+    const int64_t rb = rb0 + blockIdx.y;
+    if (rb >= sd.nrb)
+        return;
+    const Operand op = sd.op;
+    const int32_t* E = sd.E;
+    int8_t* out = (int8_t*)sd.out;
+    int32_t* dbg = sd.dbg;
     constexpr int bits = BAL ? 8 : 7;
     constexpr int NS = store_limbs<SC, BAL>();
     __shared__ uint64_t limbs[4][NS][64];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int64_t rb = rb0 + blockIdx.y, kc = blockIdx.x;
+    const int64_t kc = blockIdx.x;
     const int byte0 = 4 * t;
     const int L = byte0 >> 4;                 // fragment lane
     const int64_t r = rb * kRowBlock + (L & 15);
@@ -779,52 +930,68 @@ __global__ __launch_bounds__(256) void k_split_place(Operand op, const int32_t* 
 
 // the container for S: the smallest multiple of 8 from 8 to 48 holding it
 template <int MW, int SC, bool BAL>
-hipError_t split_place_sc(const Operand& op, const int32_t* E, int S, int64_t nkc, int8_t* out, int32_t* dbg,
-                          dim3 grid, int64_t y0, hipStream_t st)
+hipError_t split_place_sc(const SplitSide& a, const SplitSide& b, int S, int64_t nkc, dim3 grid, int64_t y0,
+                          hipStream_t st)
 {
     if constexpr (SC <= 48) {
         if (S > SC)
-            return split_place_sc<MW, SC + 8, BAL>(op, E, S, nkc, out, dbg, grid, y0, st);
-        if (dbg)
-            hipLaunchKernelGGL((k_split_place<MW, SC, BAL, true>), grid, dim3(256), 0, st, op, E, S, nkc, out, dbg, y0);
+            return split_place_sc<MW, SC + 8, BAL>(a, b, S, nkc, grid, y0, st);
+        if (a.dbg || b.dbg)
+            hipLaunchKernelGGL((k_split_place<MW, SC, BAL, true>), grid, dim3(256), 0, st, a, b, S, nkc, y0);
         else
-            hipLaunchKernelGGL((k_split_place<MW, SC, BAL, false>), grid, dim3(256), 0, st, op, E, S, nkc, out, dbg, y0);
+            hipLaunchKernelGGL((k_split_place<MW, SC, BAL, false>), grid, dim3(256), 0, st, a, b, S, nkc, y0);
         return hipGetLastError();
     } else {
         return hipErrorInvalidValue;
     }
 }
 
+// Both operands in one launch (blockIdx.z) where they are of like size: a
+// small product is bound by its launches (64^3 double-doubles, the slice
+// rule's call: 70 -> 39 us with this and the one-launch exponent pass, six
+// kernels instead of nine).  The grid covers the larger one,
+// so operands of unlike size get a launch each.
+template <class Launch>
+hipError_t split_sides(const SplitSide& a, const SplitSide& b, Launch launch)
+{
+    if (a.nrb <= 2 * b.nrb && b.nrb <= 2 * a.nrb)
+        return launch(a, b, 2u);
+    const hipError_t e = launch(a, a, 1u);
+    return e == hipSuccess ? launch(b, b, 1u) : e;
+}
+
 constexpr int split_ept(int m) { return m <= 4 ? 4 : (m == 8 ? 2 : 1); }
 
 template <int MW>
-hipError_t split_i8_m(const Operand& op, const int32_t* E, int S, int64_t nrb, int64_t nkc,
-                      int8_t* out, int32_t* dbg, bool balanced, hipStream_t st)
+hipError_t split_i8_m(const SplitSide& a, const SplitSide& b, unsigned sides, int S, int64_t nkc, bool balanced,
+                      hipStream_t st)
 {
     constexpr int EPT = split_ept(MW);
     if (nkc * (4 / EPT) > 0x7fffffff)
         return hipErrorInvalidValue;
     // word placement where a container holds S (m <= 4, S <= 48)
     constexpr bool kPlace = MW <= 4;
+    const bool dbg = a.dbg || b.dbg;
+    const int64_t nrb = std::max(a.nrb, b.nrb);
     // row blocks on the grid's second dimension, at most kMaxGridY per launch
     for (int64_t y0 = 0; y0 < nrb; y0 += kMaxGridY) {
-        const dim3 grid((unsigned)(nkc * (4 / EPT)), (unsigned)std::min<int64_t>(nrb - y0, kMaxGridY));
+        const dim3 grid((unsigned)(nkc * (4 / EPT)), (unsigned)std::min<int64_t>(nrb - y0, kMaxGridY), sides);
         if (kPlace && S >= 1 && S <= 48) {
-            const hipError_t e = balanced ? split_place_sc<MW, 8, true>(op, E, S, nkc, out, dbg, grid, y0, st)
-                                          : split_place_sc<MW, 8, false>(op, E, S, nkc, out, dbg, grid, y0, st);
+            const hipError_t e = balanced ? split_place_sc<MW, 8, true>(a, b, S, nkc, grid, y0, st)
+                                          : split_place_sc<MW, 8, false>(a, b, S, nkc, grid, y0, st);
             if (e != hipSuccess)
                 return e;
             continue;
         }
         if (balanced) {
             if (dbg)
-                hipLaunchKernelGGL((k_split_i8bal<MW, EPT, true>), grid, dim3(256), 0, st, op, E, S, nkc, out, dbg, y0);
+                hipLaunchKernelGGL((k_split_i8bal<MW, EPT, true>), grid, dim3(256), 0, st, a, b, S, nkc, y0);
             else
-                hipLaunchKernelGGL((k_split_i8bal<MW, EPT, false>), grid, dim3(256), 0, st, op, E, S, nkc, out, dbg, y0);
+                hipLaunchKernelGGL((k_split_i8bal<MW, EPT, false>), grid, dim3(256), 0, st, a, b, S, nkc, y0);
         } else if (dbg) {
-            hipLaunchKernelGGL((k_split_i8<MW, EPT, true>), grid, dim3(256), 0, st, op, E, S, nkc, out, dbg, y0);
+            hipLaunchKernelGGL((k_split_i8<MW, EPT, true>), grid, dim3(256), 0, st, a, b, S, nkc, y0);
         } else {
-            hipLaunchKernelGGL((k_split_i8<MW, EPT, false>), grid, dim3(256), 0, st, op, E, S, nkc, out, dbg, y0);
+            hipLaunchKernelGGL((k_split_i8<MW, EPT, false>), grid, dim3(256), 0, st, a, b, S, nkc, y0);
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
@@ -833,17 +1000,19 @@ hipError_t split_i8_m(const Operand& op, const int32_t* E, int S, int64_t nrb, i
     return hipSuccess;
 }
 
-hipError_t launch_split_i8(const Operand& op, int m, const int32_t* E, int S, int64_t nrb,
-                           int64_t nkc, int8_t* out, int32_t* dbg, bool balanced, hipStream_t st)
+hipError_t launch_split_i8(const SplitSide& a, const SplitSide& b, int m, int S, int64_t nkc, bool balanced,
+                           hipStream_t st)
 {
-    switch (m) {
-    case 1: return split_i8_m<1>(op, E, S, nrb, nkc, out, dbg, balanced, st);
-    case 2: return split_i8_m<2>(op, E, S, nrb, nkc, out, dbg, balanced, st);
-    case 4: return split_i8_m<4>(op, E, S, nrb, nkc, out, dbg, balanced, st);
-    case 8: return split_i8_m<8>(op, E, S, nrb, nkc, out, dbg, balanced, st);
-    case 16: return split_i8_m<16>(op, E, S, nrb, nkc, out, dbg, balanced, st);
-    default: return hipErrorInvalidValue;
-    }
+    return split_sides(a, b, [&](const SplitSide& x, const SplitSide& y, unsigned sides) {
+        switch (m) {
+        case 1: return split_i8_m<1>(x, y, sides, S, nkc, balanced, st);
+        case 2: return split_i8_m<2>(x, y, sides, S, nkc, balanced, st);
+        case 4: return split_i8_m<4>(x, y, sides, S, nkc, balanced, st);
+        case 8: return split_i8_m<8>(x, y, sides, S, nkc, balanced, st);
+        case 16: return split_i8_m<16>(x, y, sides, S, nkc, balanced, st);
+        default: return hipErrorInvalidValue;
+        }
+    });
 }
 
 template <int MW>
@@ -869,43 +1038,45 @@ hipError_t launch_validate(const Operand& op, int m, int32_t* flags, hipStream_t
 }
 
 template <int MW>
-hipError_t split_f64_m(const Operand& op, const int32_t* E, int S, int beta, int64_t nrb,
-                       int64_t nkc, double* out, int32_t* dbg, hipStream_t st)
+hipError_t split_f64_m(const SplitSide& a, const SplitSide& b, unsigned sides, int S, int beta, int64_t nkc,
+                       hipStream_t st)
 {
     constexpr int EPT = split_ept(MW);
-    const int64_t blocks = (nrb * nkc + EPT - 1) / EPT;
-    if (dbg)
-        hipLaunchKernelGGL((k_split_f64<MW, EPT, true>), dim3((unsigned)blocks), dim3(256), 0, st, op, E,
-                           S, beta, nrb, nkc, out, dbg);
+    const int64_t blocks = (std::max(a.nrb, b.nrb) * nkc + EPT - 1) / EPT;
+    const dim3 grid((unsigned)blocks, 1, sides);
+    if (a.dbg || b.dbg)
+        hipLaunchKernelGGL((k_split_f64<MW, EPT, true>), grid, dim3(256), 0, st, a, b, S, beta, nkc);
     else
-        hipLaunchKernelGGL((k_split_f64<MW, EPT, false>), dim3((unsigned)blocks), dim3(256), 0, st, op,
-                           E, S, beta, nrb, nkc, out, dbg);
+        hipLaunchKernelGGL((k_split_f64<MW, EPT, false>), grid, dim3(256), 0, st, a, b, S, beta, nkc);
     return hipGetLastError();
 }
 
-hipError_t launch_split_f64(const Operand& op, int m, const int32_t* E, int S, int beta,
-                            int64_t nrb, int64_t nkc, double* out, int32_t* dbg, hipStream_t st)
+hipError_t launch_split_f64(const SplitSide& a, const SplitSide& b, int m, int S, int beta, int64_t nkc,
+                            hipStream_t st)
 {
-    switch (m) {
-    case 1: return split_f64_m<1>(op, E, S, beta, nrb, nkc, out, dbg, st);
-    case 2: return split_f64_m<2>(op, E, S, beta, nrb, nkc, out, dbg, st);
-    case 4: return split_f64_m<4>(op, E, S, beta, nrb, nkc, out, dbg, st);
-    case 8: return split_f64_m<8>(op, E, S, beta, nrb, nkc, out, dbg, st);
-    case 16: return split_f64_m<16>(op, E, S, beta, nrb, nkc, out, dbg, st);
-    default: return hipErrorInvalidValue;
-    }
+    return split_sides(a, b, [&](const SplitSide& x, const SplitSide& y, unsigned sides) {
+        switch (m) {
+        case 1: return split_f64_m<1>(x, y, sides, S, beta, nkc, st);
+        case 2: return split_f64_m<2>(x, y, sides, S, beta, nkc, st);
+        case 4: return split_f64_m<4>(x, y, sides, S, beta, nkc, st);
+        case 8: return split_f64_m<8>(x, y, sides, S, beta, nkc, st);
+        case 16: return split_f64_m<16>(x, y, sides, S, beta, nkc, st);
+        default: return hipErrorInvalidValue;
+        }
+    });
 }
 
 template <int MW>
-hipError_t split_f64b_m(const Operand& op, const int32_t* E, int S, int beta, int nb, int64_t nrb, int64_t nkc,
-                        int8_t* out, hipStream_t st)
+hipError_t split_f64b_m(const SplitSide& a, const SplitSide& b, unsigned sides, int S, int beta, int nb, int64_t nkc,
+                        hipStream_t st)
 {
     constexpr int EPT = split_ept(MW);
     if (nkc * (4 / EPT) > 0x7fffffff)
         return hipErrorInvalidValue;
+    const int64_t nrb = std::max(a.nrb, b.nrb);
     for (int64_t y0 = 0; y0 < nrb; y0 += kMaxGridY) {
-        const dim3 grid((unsigned)(nkc * (4 / EPT)), (unsigned)std::min<int64_t>(nrb - y0, kMaxGridY));
-        hipLaunchKernelGGL((k_split_f64b<MW, EPT>), grid, dim3(256), 0, st, op, E, S, beta, nb, nkc, out, y0);
+        const dim3 grid((unsigned)(nkc * (4 / EPT)), (unsigned)std::min<int64_t>(nrb - y0, kMaxGridY), sides);
+        hipLaunchKernelGGL((k_split_f64b<MW, EPT>), grid, dim3(256), 0, st, a, b, S, beta, nb, nkc, y0);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
@@ -913,17 +1084,19 @@ hipError_t split_f64b_m(const Operand& op, const int32_t* E, int S, int beta, in
     return hipSuccess;
 }
 
-hipError_t launch_split_f64b(const Operand& op, int m, const int32_t* E, int S, int beta, int nb, int64_t nrb,
-                             int64_t nkc, int8_t* out, hipStream_t st)
+hipError_t launch_split_f64b(const SplitSide& a, const SplitSide& b, int m, int S, int beta, int nb, int64_t nkc,
+                             hipStream_t st)
 {
-    switch (m) {
-    case 1: return split_f64b_m<1>(op, E, S, beta, nb, nrb, nkc, out, st);
-    case 2: return split_f64b_m<2>(op, E, S, beta, nb, nrb, nkc, out, st);
-    case 4: return split_f64b_m<4>(op, E, S, beta, nb, nrb, nkc, out, st);
-    case 8: return split_f64b_m<8>(op, E, S, beta, nb, nrb, nkc, out, st);
-    case 16: return split_f64b_m<16>(op, E, S, beta, nb, nrb, nkc, out, st);
-    default: return hipErrorInvalidValue;
-    }
+    return split_sides(a, b, [&](const SplitSide& x, const SplitSide& y, unsigned sides) {
+        switch (m) {
+        case 1: return split_f64b_m<1>(x, y, sides, S, beta, nb, nkc, st);
+        case 2: return split_f64b_m<2>(x, y, sides, S, beta, nb, nkc, st);
+        case 4: return split_f64b_m<4>(x, y, sides, S, beta, nb, nkc, st);
+        case 8: return split_f64b_m<8>(x, y, sides, S, beta, nb, nkc, st);
+        case 16: return split_f64b_m<16>(x, y, sides, S, beta, nb, nkc, st);
+        default: return hipErrorInvalidValue;
+        }
+    });
 }
 
 }  // namespace mdg

@@ -77,8 +77,8 @@ hipError_t launch_resid(const ResPlan& r, const ResPanels& p, const GemmArgs& a,
 
 // FP64 digits of beta bits as byte planes: digit s is sum_k c_k 256^k with
 // c_k in [-128, 127], byte k in plane s nb + k, INT8 fragment order
-hipError_t launch_split_f64b(const Operand& op, int m, const int32_t* E, int S, int beta, int nb, int64_t nrb,
-                             int64_t nkc, int8_t* out, hipStream_t st);
+hipError_t launch_split_f64b(const SplitSide& a, const SplitSide& b, int m, int S, int beta, int nb, int64_t nkc,
+                             hipStream_t st);
 int res_f64_bytes(int beta);
 
 }  // namespace mdg
