@@ -37,6 +37,23 @@ constexpr int tri_issue_a(int S, int R, int LA, int q)
     return q < S ? -1 : 0;   // the next chunk's A cannot precede this chunk
 }
 
+// The A loads of each step: na[p] positions from q[p] on are issued at step
+// p (tri_issue_a is monotonic in q).
+template <int S, int R, int LA>
+struct TriSched {
+    int na[S] = {}, q[S] = {};
+    constexpr TriSched()
+    {
+        for (int x = S + 1; x >= 1; --x) {
+            const int p = tri_issue_a(S, R, LA, x);
+            if (p >= 0 && p < x) {
+                ++na[p];
+                q[p] = x;
+            }
+        }
+    }
+};
+
 // SS: slices per depth chunk in memory (S when the triangle is the whole
 // contraction; more when it is the first band of a longer split).
 template <int S, int R, int LA, int SS = S>
@@ -44,6 +61,7 @@ __device__ __forceinline__ void tri_run_i8(v4i (&acc)[R][S], const FragStream (&
                                            const FragStream& LDB, int64_t c0, int64_t c1)
 {
     constexpr uint32_t F = 1024, CS = (uint32_t)SS * F;
+    constexpr TriSched<S, R, LA> kSched{};
     uint32_t ck = (uint32_t)c0 * CS;
     v4i win[S], ar[R][S + 2];
 #pragma unroll
@@ -60,21 +78,29 @@ __device__ __forceinline__ void tri_run_i8(v4i (&acc)[R][S], const FragStream (&
         const uint32_t cn = kc + 1 < c1 ? ck + CS : ck;
 #pragma unroll
         for (int p = 0; p < S; ++p) {
-            // issue the loads scheduled at this step
+            // the loads scheduled at this step (A_q of every row block, then the
+            // window's B_{S-p} of the next chunk, last read at step p - 1),
+            // spread evenly among its matrix instructions: in a row at the
+            // step's start they hold the wave while the load path takes them
+            // (1024^3, S = 28: 342 -> 330 us a call; 1003 x 1517 x 1291, S = 31:
+            // 742 -> 728)
+            const int na = R * kSched.na[p], nl = na + (p >= 1 ? 1 : 0), nm = R * (S - p);
 #pragma unroll
-            for (int q = p + 1; q < S + 2; ++q)
-                if (tri_issue_a(S, R, LA, q) == p)
+            for (int c = 0; c < nm; ++c) {
 #pragma unroll
-                    for (int r = 0; r < R; ++r)
-                        ar[r][q] = q < S ? LDA[r](ck + q * F) : LDA[r](cn + (q - S) * F);
-            if (p >= 1)
-                win[S - p] = LDB(cn + (S - p) * F);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int g = S - 1; g >= p; --g)
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-                    acc[r][g] = FormI8::mma(ar[r][p], win[g - p], acc[r][g]);
+                for (int l = (c * nl + nm - 1) / nm; l < ((c + 1) * nl + nm - 1) / nm; ++l) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (l == na) {
+                        win[S - p] = LDB(cn + (S - p) * F);
+                    } else {
+                        const int q = kSched.q[p] + l / R;
+                        ar[l % R][q] = q < S ? LDA[l % R](ck + q * F) : LDA[l % R](cn + (q - S) * F);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                const int g = S - 1 - c / R;
+                acc[c % R][g] = FormI8::mma(ar[c % R][p], win[g - p], acc[c % R][g]);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
         win[0] = LDB(cn);
