@@ -30,6 +30,7 @@ struct ResTables {
     int8_t *VA, *VB, *W;
     float2* pc;
     int Lp, Np, KD, pl16;
+    int packed;
 };
 
 struct ResShape {   // plan values the kernels use
@@ -175,11 +176,17 @@ __global__ __launch_bounds__(512) void k_res_tables(ResShape s, ResTables t)
         den[tid] = umod(r * crt, p, inv);
     }
     __syncthreads();
-    int8_t* W = t.W + (int64_t)i * t.Lp * t.Np;
-    for (int e = tid; e < t.Lp * t.Np; e += 512) {
-        const int tau = e / t.Np, j = e % t.Np;
+    // packed (res_packed): two primes to a 16 x 32 tile, the even one's rows
+    // 0 .. 7 and columns 0 .. 15, the odd one's the others
+    const bool packed = t.packed;
+    const int half = packed ? i & 1 : 0;
+    int8_t* W = t.W + (packed ? (int64_t)(i / 2) * 512 : (int64_t)i * t.Lp * t.Np);
+    // an odd number of primes: the last one fills the missing one's half
+    const int rows = packed ? (half == 0 && i + 1 == s.P ? 16 : 8) : t.Lp;
+    for (int e = tid; e < rows * t.Np; e += 512) {
+        const int tau = e / t.Np, j = e % t.Np - 16 * half;
         int v = 0;
-        if (tau < L && j < s.N) {
+        if (tau < L && j >= 0 && j < s.N) {
             const int xi = (j + 1) / 2;
             if (xi == 0) {
                 v = (tau & 1) ? 0 : G[tau / 2];
@@ -190,7 +197,7 @@ __global__ __launch_bounds__(512) void k_res_tables(ResShape s, ResTables t)
             }
             v = centred(umod(v * den[xi], p, inv), p);
         }
-        W[e] = (int8_t)v;
+        W[8 * half * t.Np + e] = (int8_t)v;
     }
 }
 
@@ -613,6 +620,17 @@ __global__ __launch_bounds__(256, 1) void k_res_gemm(ResGemmArgs a)
 // low bits of the Chinese remainder's factors (M / p < 2^56)
 constexpr int kResSplit = 27;
 
+// a + b over the wave's two halves: lanes 0 .. 31 get a(l) + a(l + 32), lanes
+// 32 .. 63 b(l - 32) + b(l)
+__device__ __forceinline__ double add_halves(double a, double b)
+{
+    const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
+    const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)ua, (uint32_t)ub, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(ua >> 32), (uint32_t)(ub >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]) +
+           __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]);
+}
+
 struct ResFinalArgs {
     const char* R;
     const int32_t* Rb;
@@ -639,7 +657,12 @@ struct ResFinalArgs {
 // significant), pass 16 at a time through LDS to the lane that folds their
 // output, and enter a signed 96-bit window whose low 32 bits leave as limbs;
 // then the limbs are rounded (as k_gemm_final's).
-template <int NL, int NT, bool FIX>
+// PK (L <= 8): two primes at a time, one on the weights' rows 0 .. 7 and
+// points 0 .. 15 (lanes q = 0, 1), the other on the rest (q = 2, 3); the two
+// halves' sums meet at the end, each half of the wave keeping every other
+// row (double-doubles 2048^3, 8 primes of 9 points: a step of three products
+// 3216 -> 3050 us).
+template <int NL, int NT, bool FIX, bool PK>
 __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void k_res_final(ResFinalArgs a)
 {
     __shared__ int64_t coef[4][16][64];
@@ -668,15 +691,17 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void k_res_final(ResFinalArgs
     uint32_t wl = (uint32_t)wh;
     wh >>= 32;
     int bit = 0, k = 0;                             // position of the next coefficient, limbs done
-    const int nj = a.Np / 32, its = a.P * nj;
-    // points past a prime's last one weigh zero: they read the next prime's
+    const int nj = PK ? 1 : a.Np / 32, its = PK ? (a.P + 1) / 2 : a.P * nj;
+    const int half = PK ? q >> 1 : 0;   // the prime of this lane's points and coefficients
+    // (32-bit offsets: below 32 planes.)  Points past a prime's last one weigh
+    // zero: they read the next prime's
     // plane, or past the last prime zeros (out of the descriptor's range)
     uint32_t voff[8], nx[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-        voff[j] = (uint32_t)((8 * q + j) * a.psR + wave * 64 + n * 4);   // below 32 planes
+        voff[j] = (uint32_t)(((PK ? half * a.N + 8 * (q & 1) : 8 * q) + j) * a.psR + wave * 64 + n * 4);
     auto load = [&](int i, int j0) {
-        const int64_t pt = (int64_t)i * a.N + j0;
+        const int64_t pt = (int64_t)(PK ? 2 * i : i) * a.N + j0;
         const int64_t left = ((int64_t)a.P * a.N - pt) * a.psR - blk * 256;
         const __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char*>(a.R) + pt * a.psR + blk * 256, 0, (int)min(left, (int64_t)0xffffff00), 0x00020000);
@@ -702,11 +727,11 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void k_res_final(ResFinalArgs
 #pragma unroll
             for (int x = 0; x < NT; ++x)   // rows past Lp: the last tile again (not kept)
                 wf[x] = *(const int64_t*)(a.W + (uint32_t)((i * a.Lp + min(t0 + 16 * x, a.Lp - 16) + n) * a.Np + jb * 32 +
-                                                           8 * q));
+                                                           8 * q));   // PK: Lp = 16, Np = 32
             const int i0 = i;
             const bool first = jb == 0, last = jb + 1 == nj;
             jb = last ? 0 : jb + 1;
-            i = last ? (i + 1 == a.P ? 0 : i + 1) : i;
+            i = last ? (i + 1 == (PK ? its : a.P) ? 0 : i + 1) : i;
             load(i, jb * 32);
             transpose4(d[0], d[1], d[2], d[3]);
             transpose4(d[4], d[5], d[6], d[7]);
@@ -721,7 +746,8 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void k_res_final(ResFinalArgs
                         acc[x][y] = __builtin_amdgcn_mfma_i32_16x16x32_i8(wf[x], df, acc[x][y], 0, 0, 0);
                 }
             if (last) {
-                const double Wh = a.Wh[i0], Wl = a.Wl[i0];
+                const double Wh = PK ? (half ? a.Wh[2 * i0 + 1] : a.Wh[2 * i0]) : a.Wh[i0];
+                const double Wl = PK ? (half ? a.Wl[2 * i0 + 1] : a.Wl[2 * i0]) : a.Wl[i0];
 #pragma unroll
                 for (int x = 0; x < NT; ++x)
 #pragma unroll
@@ -734,10 +760,21 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void k_res_final(ResFinalArgs
                         }
             }
         }
+        if constexpr (PK) {
+            // rows 2 y and 2 y + 1: lanes 0 .. 31 end with both halves' sum
+            // of row 2 y, lanes 32 .. 63 of row 2 y + 1
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+#pragma unroll
+                for (int o = 0; o < 4; ++o) {
+                    hi[0][4 * y + o] = add_halves(hi[0][8 * y + o], hi[0][8 * y + 4 + o]);
+                    lo[0][4 * y + o] = add_halves(lo[0][8 * y + o], lo[0][8 * y + 4 + o]);
+                }
+        }
 #pragma unroll
         for (int x = NT - 1; x >= 0; --x) {
 #pragma unroll
-            for (int y = 0; y < 4; ++y)
+            for (int y = 0; y < (PK ? 2 : 4); ++y)
 #pragma unroll
                 for (int o = 0; o < 4; ++o) {
                     constexpr double kMagic = 6755399441055744.0;   // 1.5 2^52
@@ -746,7 +783,7 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void k_res_final(ResFinalArgs
                     const double kq = __builtin_rint(__builtin_fma(h, kSplit, z) * a.invM);
                     const double hr = __builtin_fma(-kq, a.Mh, h) + kMagic, zr = __builtin_fma(-kq, a.Ml, z) + kMagic;
                     const int64_t bits = __builtin_bit_cast(int64_t, kMagic);
-                    coef[wave][4 * q + o][y * 16 + n] =
+                    coef[wave][PK ? 4 * (q & 1) + o : 4 * q + o][(PK ? 2 * y + half : y) * 16 + n] =
                         (int64_t)((uint64_t)(__builtin_bit_cast(int64_t, hr) - bits) << kResSplit) +
                         (__builtin_bit_cast(int64_t, zr) - bits);
                 }
@@ -814,33 +851,49 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void k_res_final(ResFinalArgs
 }
 
 template <int NL>
-hipError_t launch_res_final(const ResFinalArgs& a, hipStream_t st)
+hipError_t launch_res_final(const ResFinalArgs& a, bool packed, hipStream_t st)
 {
     const dim3 blocks((unsigned)((int64_t)a.nbA * a.nbB));
+    if constexpr (NL <= 8)
+        if (packed) {
+            if (a.g.fixX)
+                hipLaunchKernelGGL((k_res_final<NL, 1, true, true>), blocks, dim3(256), 0, st, a);
+            else
+                hipLaunchKernelGGL((k_res_final<NL, 1, false, true>), blocks, dim3(256), 0, st, a);
+            return hipGetLastError();
+        }
+    if (packed)   // L <= 8 coefficients of at most 24 bits fold into 8 limbs
+        return hipErrorInvalidValue;
     const bool two = a.L > 16;   // two tiles of 16 coefficients at once
     if (a.g.fixX)
-        hipLaunchKernelGGL((two ? k_res_final<NL, 2, true> : k_res_final<NL, 1, true>), blocks, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((two ? k_res_final<NL, 2, true, false> : k_res_final<NL, 1, true, false>), blocks, dim3(256), 0,
+                           st, a);
     else
-        hipLaunchKernelGGL((two ? k_res_final<NL, 2, false> : k_res_final<NL, 1, false>), blocks, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((two ? k_res_final<NL, 2, false, false> : k_res_final<NL, 1, false, false>), blocks, dim3(256),
+                           0, st, a);
     return hipGetLastError();
 }
 
 // limbs that hold |X| < K 2^(beta (S + 1) + 1) and its sign, rounded up to
 // an instantiated count
-hipError_t dispatch_res_final(const ResFinalArgs& a, int nl, hipStream_t st)
+hipError_t dispatch_res_final(const ResFinalArgs& a, int nl, bool packed, hipStream_t st)
 {
-    if (nl <= 4) return launch_res_final<4>(a, st);
-    if (nl <= 6) return launch_res_final<6>(a, st);
-    if (nl <= 8) return launch_res_final<8>(a, st);
-    if (nl <= 10) return launch_res_final<10>(a, st);
-    if (nl <= 12) return launch_res_final<12>(a, st);
-    if (nl <= 16) return launch_res_final<16>(a, st);
-    if (nl <= 20) return launch_res_final<20>(a, st);
-    if (nl <= 24) return launch_res_final<24>(a, st);
-    if (nl <= 28) return launch_res_final<28>(a, st);
-    if (nl <= 32) return launch_res_final<32>(a, st);
+    if (nl <= 4) return launch_res_final<4>(a, packed, st);
+    if (nl <= 6) return launch_res_final<6>(a, packed, st);
+    if (nl <= 8) return launch_res_final<8>(a, packed, st);
+    if (nl <= 10) return launch_res_final<10>(a, packed, st);
+    if (nl <= 12) return launch_res_final<12>(a, packed, st);
+    if (nl <= 16) return launch_res_final<16>(a, packed, st);
+    if (nl <= 20) return launch_res_final<20>(a, packed, st);
+    if (nl <= 24) return launch_res_final<24>(a, packed, st);
+    if (nl <= 28) return launch_res_final<28>(a, packed, st);
+    if (nl <= 32) return launch_res_final<32>(a, packed, st);
     return hipErrorInvalidValue;
 }
+
+// Few coefficients (L <= 8, so N <= 15 points): two primes share a tile of
+// the interpolation.
+bool res_packed(const ResPlan& r) { return r.L <= 8; }
 
 // scratch layout of one panel
 struct ResLayout {
@@ -861,6 +914,7 @@ void res_layout(const ResPlan& r, int64_t mr, int64_t nc, int nchunk, int64_t K,
     l.t.pl16 = (r.planes() + 15) / 16 * 16;
     l.t.Lp = (r.L + 15) / 16 * 16;
     l.t.Np = (r.N + 31) / 32 * 32;
+    l.t.packed = res_packed(r);
     size_t at = 0;
     auto take = [&](size_t n) {
         const size_t o = at;
@@ -1110,7 +1164,7 @@ hipError_t launch_resid(const ResPlan& r, const ResPanels& pn, const GemmArgs& g
             fa.nbB = ga.nbB;
             fa.r0 = r0;
             fa.c0 = c0;
-            if ((e = dispatch_res_final(fa, nl, st)) != hipSuccess)
+            if ((e = dispatch_res_final(fa, nl, res_packed(r), st)) != hipSuccess)
                 return e;
         }
     }
