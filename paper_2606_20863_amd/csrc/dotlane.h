@@ -160,9 +160,9 @@ __device__ __forceinline__ void lane_round(const int64_t* dsum, int scale, int m
     }
     carry_cols<CW>(x);
     uint32_t L[NL];
-    double sgn = to_limbs<CW>(x, L) ? -1.0 : 1.0;
+    int32_t sg = to_limbs_signed<CW>(x, L);
     for (int t = 0; t < m; ++t)
-        out[t * pso] = rn_next(L, sgn, scale);
+        out[t * pso] = rn_signed(L, sg, scale);
 }
 
 template <int MW, int SC, bool BAL>

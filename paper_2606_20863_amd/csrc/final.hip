@@ -25,7 +25,7 @@ constexpr int kRing = 8;   // diagonal sums in flight per thread
 // NL 32-bit limbs (NL >= the fold width, so the window ends as the sign)
 // stay in registers: the limb index is the unrolled loop's; the diagonal
 // index is a runtime count, served from a ring of prefetched sums.  Then the
-// magnitude is rounded greedily, word by word (the triangle kernels'
+// integer is rounded greedily, word by word (the triangle kernels'
 // register renormalisation).  With a debug buffer the sums are also written
 // there as [S][M][N].  FIX: the folded integer itself (two's complement
 // limbs, the window's sign past NL) and its scale go to a.fixX and
@@ -93,20 +93,11 @@ __global__ __launch_bounds__(256) void k_gemm_final(GemmArgs a)
         a.fixScale[e] = a.E[i] + a.F[j] - a.beta * (a.S + 1);
         return;
     }
-    // magnitude (two's complement negation when X < 0)
-    const bool neg = win < 0;
-    uint64_t cy = 1;
-#pragma unroll
-    for (int k = 0; k < NL; ++k) {
-        const uint64_t v = (uint64_t)(~L[k]) + cy;
-        cy = v >> 32;
-        L[k] = neg ? (uint32_t)v : L[k];
-    }
-    double sgn = neg ? -1.0 : 1.0;
+    int32_t sg = win < 0 ? -1 : 0;
     int scale = ok ? a.E[i] + a.F[j] - a.beta * (a.S + 1) : 0;
     double* out = a.C + (ok ? i * a.ldc + j : 0);
     for (int w = 0; w < a.m; ++w) {
-        const double wv = rn_next(L, sgn, scale);
+        const double wv = rn_signed(L, sg, scale);
         if (ok)
             out[w * a.psc] = wv;
     }

@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256) void k_fixed_add(int64_t count, int nlimb, con
     }
 }
 
-// Magnitude in NL >= nlimb register limbs (sign-extended), then the greedy
+// NL >= nlimb register limbs (sign-extended), then the greedy
 // rounding steps of the product's own fold.
 template <int NL>
 __global__ __launch_bounds__(256) void k_fixed_round(int m, int64_t count, int nlimb, const int32_t* X,
@@ -81,17 +81,10 @@ __global__ __launch_bounds__(256) void k_fixed_round(int m, int64_t count, int n
 #pragma unroll
     for (int k = 0; k < NL; ++k)
         L[k] = k < nlimb ? (uint32_t)X[(int64_t)k * count + e] : (neg ? 0xffffffffu : 0u);
-    uint64_t cy = 1;
-#pragma unroll
-    for (int k = 0; k < NL; ++k) {
-        const uint64_t v = (uint64_t)(~L[k]) + cy;
-        cy = v >> 32;
-        L[k] = neg ? (uint32_t)v : L[k];
-    }
-    double sgn = neg ? -1.0 : 1.0;
+    int32_t sg = neg ? -1 : 0;
     int sc = scale[e];
     for (int w = 0; w < m; ++w)
-        C[w * psc + e] = rn_next(L, sgn, sc);
+        C[w * psc + e] = rn_signed(L, sg, sc);
 }
 
 // C = the sum of a product's depth parts (each nlimb limb planes of M N
@@ -118,19 +111,11 @@ __global__ __launch_bounds__(256) void k_parts_round(int m, int64_t M, int64_t N
         L[k] = (uint32_t)cy;
         cy >>= 32;
     }
-    const bool neg = cy < 0 || (int32_t)L[NL - 1] < 0;
-    uint64_t up = 1;
-#pragma unroll
-    for (int k = 0; k < NL; ++k) {
-        const uint64_t v = (uint64_t)(~L[k]) + up;
-        up = v >> 32;
-        L[k] = neg ? (uint32_t)v : L[k];
-    }
-    double sgn = neg ? -1.0 : 1.0;
+    int32_t sg = cy < 0 ? -1 : 0;
     int sc = scale[e];
     double* out = C + e / N * ldc + e % N;
     for (int w = 0; w < m; ++w)
-        out[w * psc] = rn_next(L, sgn, sc);
+        out[w * psc] = rn_signed(L, sg, sc);
 }
 
 unsigned blocks_of(int64_t count) { return (unsigned)((count + 255) / 256); }

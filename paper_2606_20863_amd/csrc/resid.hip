@@ -832,19 +832,11 @@ __global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void k_res_final(ResFinalArgs
         ga.fixScale[at] = scale0;
         return;
     }
-    const bool neg = wh < 0;
-    uint64_t cy = 1;
-#pragma unroll
-    for (int x = 0; x < NL; ++x) {
-        const uint64_t v = (uint64_t)(~L[x]) + cy;
-        cy = v >> 32;
-        L[x] = neg ? (uint32_t)v : L[x];
-    }
-    double sgn = neg ? -1.0 : 1.0;
+    int32_t sg = wh < 0 ? -1 : 0;
     int scale = scale0;
     double* out = ga.C + (ok ? i * ga.ldc + j : 0);
     for (int x = 0; x < ga.m; ++x) {
-        const double wv = rn_next(L, sgn, scale);
+        const double wv = rn_signed(L, sg, scale);
         if (ok)
             out[x * ga.psc] = wv;
     }

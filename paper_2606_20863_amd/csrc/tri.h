@@ -154,16 +154,16 @@ __device__ __forceinline__ void tri_fold(const v4i (&acc)[R][S], int64_t (&x)[4 
 // Greedy renormalisation of the lane's 4 R outputs, their steps interleaved.
 // FIX: instead, the exact integers as two's complement limb planes
 // (a.fixX[k * M N + i N + j], limbs past the register ones filled with the
-// sign) and their scales (a.fixScale[i N + j]).  FAST: rn_next's fixed-place
-// alignment of the remainders (off where the kernel has no registers left).
+// sign) and their scales (a.fixScale[i N + j]).
 // G: outputs whose steps interleave (groups of G one after the other).
-template <int S, int R, int B, bool FIX = false, bool FAST = true, int G = 4 * R>
+template <int S, int R, int B, bool FIX = false, int G = 4 * R>
 __device__ __forceinline__ void tri_outputs(int64_t (&x)[4 * R][(Tri<S, B>::kCols)], const GemmArgs& a,
                                             int64_t rb0, int64_t cb, int lane)
 {
     constexpr int NL = Tri<S, B>::kLimbs, NO = 4 * R;
     uint32_t L[NO][NL];
-    double sgn[NO], *out[NO];
+    double* out[NO];
+    int32_t sg[NO];
     int scale[NO];
     bool ok[NO];
 #pragma unroll
@@ -172,30 +172,21 @@ __device__ __forceinline__ void tri_outputs(int64_t (&x)[4 * R][(Tri<S, B>::kCol
         ok[n] = i < a.M && j < a.N;
         scale[n] = ok[n] ? a.E[i] + a.F[j] - B * (S + 1) : 0;
         out[n] = a.C + (ok[n] ? i * a.ldc + j : 0);
-        sgn[n] = to_limbs<Tri<S, B>::kCW>(x[n], L[n]) ? -1.0 : 1.0;
+        sg[n] = to_limbs_signed<Tri<S, B>::kCW>(x[n], L[n]);
     }
     if constexpr (FIX) {
         const int64_t count = a.M * a.N;
 #pragma unroll
         for (int n = 0; n < NO; ++n) {
             const int64_t e = ((rb0 + n / 4) * 16 + FormI8::row(lane, n % 4)) * a.N + cb * 16 + (lane & 15);
-            const bool neg = sgn[n] < 0.0;
-            uint64_t cy = 1;
-#pragma unroll
-            for (int k = 0; k < NL; ++k) {
-                const uint64_t v = (uint64_t)(~L[n][k]) + cy;
-                cy = v >> 32;
-                L[n][k] = neg ? (uint32_t)v : L[n][k];
-            }
             if (!ok[n])
                 continue;
-            for (int k = 0; k < a.fixNL; ++k) {
-                uint32_t v = neg ? 0xffffffffu : 0u;
 #pragma unroll
-                for (int q = 0; q < NL; ++q)
-                    v = q == k ? L[n][q] : v;
-                a.fixX[(int64_t)k * count + e] = (int32_t)v;
-            }
+            for (int k = 0; k < NL; ++k)
+                if (k < a.fixNL)
+                    a.fixX[(int64_t)k * count + e] = (int32_t)L[n][k];
+            for (int k = NL; k < a.fixNL; ++k)
+                a.fixX[(int64_t)k * count + e] = sg[n];
             a.fixScale[e] = scale[n];
         }
         return;
@@ -206,7 +197,7 @@ __device__ __forceinline__ void tri_outputs(int64_t (&x)[4 * R][(Tri<S, B>::kCol
         for (int t = 0; t < a.m; ++t) {
 #pragma unroll
             for (int n = g0; n < g0 + G; ++n) {
-                const double wv = rn_next<NL, FAST>(L[n], sgn[n], scale[n]);
+                const double wv = rn_signed(L[n], sg[n], scale[n]);
                 if (ok[n])
                     out[n][t * a.psc] = wv;
             }
