@@ -856,7 +856,7 @@ hipError_t launch_exp_set(const int32_t* Ein, const int32_t* hi, int64_t R, int 
 }
 
 // Entries per thread of the splits: fewer when an entry has more words.
-// INT8 split by word placement (the digits of split.h), m <= 4: the same
+// INT8 split by word placement (the digits of split.h): the same
 // threads, entries and stores as k_split_i8 / k_split_i8bal with four
 // entries per thread, the four entries of a thread being the four bytes of
 // each digit word.  Each word's truncated significand is placed at its bit
@@ -888,14 +888,23 @@ __global__ __launch_bounds__(256) void k_split_place(SplitSide sa, SplitSide sb,
     const int Er = row_ok ? E[r] : 0;
     const int kn = Er + 1075 - bits * S, pad = bits * (SC - S);
 
-    double x[4][MW];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    // one entry's words (zeros outside)
+    auto load = [&](double (&x)[MW], int q) {
         const int64_t k = kbase + q;
         const bool ok = row_ok && k < op.K;
 #pragma unroll
         for (int w = 0; w < MW; ++w)
-            x[q][w] = ok ? op.p[w * op.ps + r * op.sr + k * op.sk] : 0.0;
+            x[w] = ok ? op.p[w * op.ps + r * op.sr + k * op.sk] : 0.0;
+    };
+    // few words: all four entries' in flight at once; many: the next one's
+    // while one is cut
+    double x[MW <= 4 ? 4 : 2][MW];
+    if constexpr (MW <= 4) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            load(x[q], q);
+    } else {
+        load(x[0], 0);
     }
     LdsLimbs Ls{&limbs[wave][0][lane]};
 #pragma unroll
@@ -907,10 +916,13 @@ __global__ __launch_bounds__(256) void k_split_place(SplitSide sa, SplitSide sb,
         xs[s] = 0;
     unroll<4>([&](auto QQ) {
         constexpr int q = decltype(QQ)::value;
+        constexpr int b = MW <= 4 ? q : q & 1;
+        if constexpr (MW > 4 && q < 3)
+            load(x[b ^ 1], q + 1);
         if constexpr (BAL)
-            digits_bal<q, MW, SC>(x[q], kn, pad, xs, Ls);
+            digits_bal<q, MW, SC>(x[b], kn, pad, xs, Ls);
         else
-            digits_sm<q, MW, SC>(x[q], kn, pad, xs, Ls);
+            digits_sm<q, MW, SC>(x[b], kn, pad, xs, Ls);
     });
     uint32_t* o = reinterpret_cast<uint32_t*>(out + ((rb * nkc + kc) * (int64_t)S) * 1024 + byte0);
 #pragma unroll
@@ -928,12 +940,20 @@ __global__ __launch_bounds__(256) void k_split_place(SplitSide sa, SplitSide sb,
     }
 }
 
-// the container for S: the smallest multiple of 8 from 8 to 48 holding it
+// Containers (multiples of 8 digits) of the word-placement split: those that
+// the slice rule reaches for MW words with room on both sides.  Elsewhere
+// every word is cut at every limb, which costs S MW steps per entry instead
+// of S + MW (both operands of a 1024^3 product of 16 words, S = 105: 346 us
+// against 149; of 8 words, S = 52: 104 against 65).
+constexpr int place_lo(int mw) { return mw <= 4 ? 8 : (mw == 8 ? 48 : 96); }
+constexpr int place_hi(int mw) { return mw <= 4 ? 48 : (mw == 8 ? 64 : 128); }
+
+// the container for S: the smallest one holding it
 template <int MW, int SC, bool BAL>
 hipError_t split_place_sc(const SplitSide& a, const SplitSide& b, int S, int64_t nkc, dim3 grid, int64_t y0,
                           hipStream_t st)
 {
-    if constexpr (SC <= 48) {
+    if constexpr (SC <= place_hi(MW)) {
         if (S > SC)
             return split_place_sc<MW, SC + 8, BAL>(a, b, S, nkc, grid, y0, st);
         if (a.dbg || b.dbg)
@@ -969,16 +989,18 @@ hipError_t split_i8_m(const SplitSide& a, const SplitSide& b, unsigned sides, in
     constexpr int EPT = split_ept(MW);
     if (nkc * (4 / EPT) > 0x7fffffff)
         return hipErrorInvalidValue;
-    // word placement where a container holds S (m <= 4, S <= 48)
-    constexpr bool kPlace = MW <= 4;
+    // word placement where a container holds S
+    const bool place = S > place_lo(MW) - 8 && S <= place_hi(MW);
     const bool dbg = a.dbg || b.dbg;
     const int64_t nrb = std::max(a.nrb, b.nrb);
     // row blocks on the grid's second dimension, at most kMaxGridY per launch
     for (int64_t y0 = 0; y0 < nrb; y0 += kMaxGridY) {
-        const dim3 grid((unsigned)(nkc * (4 / EPT)), (unsigned)std::min<int64_t>(nrb - y0, kMaxGridY), sides);
-        if (kPlace && S >= 1 && S <= 48) {
-            const hipError_t e = balanced ? split_place_sc<MW, 8, true>(a, b, S, nkc, grid, y0, st)
-                                          : split_place_sc<MW, 8, false>(a, b, S, nkc, grid, y0, st);
+        const unsigned gy = (unsigned)std::min<int64_t>(nrb - y0, kMaxGridY);
+        const dim3 grid((unsigned)(nkc * (4 / EPT)), gy, sides);
+        if (place) {
+            const dim3 g4((unsigned)nkc, gy, sides);   // four entries per thread
+            const hipError_t e = balanced ? split_place_sc<MW, place_lo(MW), true>(a, b, S, nkc, g4, y0, st)
+                                          : split_place_sc<MW, place_lo(MW), false>(a, b, S, nkc, g4, y0, st);
             if (e != hipSuccess)
                 return e;
             continue;

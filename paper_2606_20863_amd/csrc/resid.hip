@@ -49,8 +49,8 @@ __device__ __forceinline__ int centred(int r, int p) { return r > p / 2 ? r - p 
 
 constexpr int kResGroups = 256;   // workgroups of the products: one per compute unit
 
-// One workgroup of 512 threads per prime, and one for the last diagonal's
-// rows.  Point j: 0, +1, -1, +2, -2, ..  The interpolation weights come from
+// Two workgroups of 512 threads per prime, one for the evaluation weights and
+// one for the interpolation's, and one for the last diagonal's rows.  Point j: 0, +1, -1, +2, -2, ..  The interpolation weights come from
 // Q(x) = x G(x^2), G(z) = prod_i (z - i^2): Q / (x - x_j) is G(x^2) for the
 // point 0 and (x^2 + x_j x) H_i(x^2), H_i = G / (z - i^2), for +-i, with
 // Q'(x_j) = G(0) or 2 i^2 H_i(i^2).  The Chinese remainder's factor
@@ -58,7 +58,7 @@ constexpr int kResGroups = 256;   // workgroups of the products: one per compute
 // hundreds, and nothing has to be kept between calls.
 __global__ __launch_bounds__(512) void k_res_tables(ResShape s, ResTables t)
 {
-    const int tid = threadIdx.x, i = blockIdx.x;
+    const int tid = threadIdx.x, i = blockIdx.x >> 1;
     if (i == s.P) {
         // last diagonal: one digit per plane, modulus 256 (the digit itself).
         // A plane q takes digit 2 q, B plane q the digit that completes S - 1.
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(512) void k_res_tables(ResShape s, ResTables t)
     const int p = d_primes[i], L = s.L;
     const float inv = 1.0f / (float)p;
     // evaluation weights: thread (part, j) takes a quarter of the digits
-    {
+    if ((blockIdx.x & 1) == 0) {
         const int j = tid & 127, part = tid >> 7;
         const int per = (t.KD + 3) / 4;
         for (int jj = j; jj < s.N; jj += 128) {
@@ -128,13 +128,15 @@ __global__ __launch_bounds__(512) void k_res_tables(ResShape s, ResTables t)
             }
         }
     }
+    if ((blockIdx.x & 1) == 0)
+        return;
     // G, one factor (z - i^2) after the other
     if (tid < 96)
         G[tid] = tid == 0;
-    if (tid == 0) {
+    if (tid == 511) {
         int m = 1;
         for (int q = 0; q < s.P; ++q)
-            m = q == i ? m : umod(m * (d_primes[q] % p), p, inv);
+            m = q == i ? m : umod(m * d_primes[q], p, inv);
         int e = p - 2, r = 1;   // m^(p-2)
         for (; e; e >>= 1) {
             r = (e & 1) ? umod(r * m, p, inv) : r;
@@ -1057,7 +1059,7 @@ hipError_t launch_resid(const ResPlan& r, const ResPanels& pn, const GemmArgs& g
     ResLayout l;
     res_layout(r, pn.mr, pn.nc, pn.nchunk, K, scratch, l);
     const ResShape s{r.L, r.N, r.P, r.SB, r.nb, r.S, r.beta, r.nbd};
-    hipLaunchKernelGGL(k_res_tables, dim3(r.P + 1), dim3(512), 0, st, s, l.t);
+    hipLaunchKernelGGL(k_res_tables, dim3(2 * r.P + 1), dim3(512), 0, st, s, l.t);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
