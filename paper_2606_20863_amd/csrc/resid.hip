@@ -258,41 +258,52 @@ struct ResEvalArgs {
 // stores 16 depths at once.  Residue planes keep the digits' fragment order
 // (16 rows x 64 depths per 1 KB), their depth padded with zeros to an even
 // number of chunks (the products take two at a time).
+// KT: 64-digit operands (v_mfma_i32_16x16x64_i8); 0: up to 32 digits, eight
+// per lane (v_mfma_i32_16x16x32_i8), half the loads, transposes and registers:
+// four waves per SIMD instead of three (4096^2 entries, 27 digits to 164
+// planes: 735 -> 628 us, 5.1 TB/s).
 template <int KT>
 __global__ __launch_bounds__(256) void k_res_eval(ResEvalArgs a)
 {
+    constexpr int KN = KT ? KT : 1, PL = KT ? 16 : 8;   // operands, digits per lane and operand
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = lane & 15, q = lane >> 4;
     const int64_t rb = blockIdx.y;
     const int kc = blockIdx.x;
     const char* src = a.dig + (rb * a.nkc + kc) * ((int64_t)a.SB * 1024) + (wave * 16 + n) * 16;
-    v4i T[KT][16];   // T[kt][e]: digits 64 kt + 16 q .. + 15 of depth e
+    uint32_t T[KN][16][PL / 4];   // T[kt][e]: digits 4 PL kt + PL q .. + PL - 1 of depth e
 #pragma unroll
-    for (int kt = 0; kt < KT; ++kt) {
-        v4i D[16];
+    for (int kt = 0; kt < KN; ++kt) {
+        v4i D[PL];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int s = 64 * kt + 16 * q + i;
+        for (int i = 0; i < PL; ++i) {
+            const int s = 4 * PL * kt + PL * q + i;
             D[i] = s < a.SB && kc < a.nkc ? *(const v4i*)(src + (int64_t)s * 1024) : v4i{0, 0, 0, 0};
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int g = 0; g < PL / 4; ++g) {
                 uint32_t w0 = D[4 * g][c], w1 = D[4 * g + 1][c], w2 = D[4 * g + 2][c], w3 = D[4 * g + 3][c];
                 transpose4(w0, w1, w2, w3);
-                T[kt][4 * c][g] = (int)w0;
-                T[kt][4 * c + 1][g] = (int)w1;
-                T[kt][4 * c + 2][g] = (int)w2;
-                T[kt][4 * c + 3][g] = (int)w3;
+                T[kt][4 * c][g] = w0;
+                T[kt][4 * c + 1][g] = w1;
+                T[kt][4 * c + 2][g] = w2;
+                T[kt][4 * c + 3][g] = w3;
             }
     }
     char* dst = a.out + (rb * a.nkr + kc) * 1024 + (wave * 16 + n) * 16;
     for (int t = 0; t < a.planes; t += 16) {
-        v4i vf[KT];
+        const int8_t* V = a.V + (int64_t)(t + n) * a.KD + PL * q;
+        int64_t vh = 0;
+        v4i vf[KN];
+        if constexpr (KT == 0) {
+            vh = *(const int64_t*)V;
+        } else {
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt)
-            vf[kt] = *(const v4i*)(a.V + (int64_t)(t + n) * a.KD + 64 * kt + 16 * q);
+            for (int kt = 0; kt < KN; ++kt)
+                vf[kt] = *(const v4i*)(V + 64 * kt);
+        }
         float inv[4];
         int negp[4];
 #pragma unroll
@@ -308,9 +319,18 @@ __global__ __launch_bounds__(256) void k_res_eval(ResEvalArgs a)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 acc[e] = v4i{0, 0, 0, 0};
+                if constexpr (KT == 0) {
+                    const uint32_t* d = T[0][4 * g + e];
+                    acc[e] = __builtin_amdgcn_mfma_i32_16x16x32_i8(vh, (int64_t)(((uint64_t)d[1] << 32) | d[0]), acc[e], 0,
+                                                                   0, 0);
+                } else {
 #pragma unroll
-                for (int kt = 0; kt < KT; ++kt)
-                    acc[e] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf[kt], T[kt][4 * g + e], acc[e], 0, 0, 0);
+                    for (int kt = 0; kt < KN; ++kt) {
+                        const uint32_t* d = T[kt][4 * g + e];
+                        acc[e] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                            vf[kt], v4i{(int)d[0], (int)d[1], (int)d[PL / 4 - 2], (int)d[PL / 4 - 1]}, acc[e], 0, 0, 0);
+                    }
+                }
             }
 #pragma unroll
             for (int o = 0; o < 4; ++o)
@@ -858,7 +878,9 @@ hipError_t launch_res_final(const ResFinalArgs& a, bool packed, hipStream_t st)
         }
     if (packed)   // L <= 8 coefficients of at most 24 bits fold into 8 limbs
         return hipErrorInvalidValue;
-    const bool two = a.L > 16;   // two tiles of 16 coefficients at once
+    // two tiles of 16 coefficients at once (four, for L > 32, leave one wave
+    // per SIMD: 549 -> 761 us at hexa-double 1024^3)
+    const bool two = a.L > 16;
     if (a.g.fixX)
         hipLaunchKernelGGL((two ? k_res_final<NL, 2, true, false> : k_res_final<NL, 1, true, false>), blocks, dim3(256), 0,
                            st, a);
@@ -1103,7 +1125,8 @@ hipError_t launch_resid(const ResPlan& r, const ResPanels& pn, const GemmArgs& g
             ResEvalArgs ey = ea;
             ey.dig += y0 * g.nkc * (int64_t)r.SB * 1024;
             ey.out += y0 * nkr * 1024;
-            switch (r.kt()) {
+            switch (r.SB <= 32 ? 0 : r.kt()) {
+            case 0: hipLaunchKernelGGL((k_res_eval<0>), grid, dim3(256), 0, st, ey); break;
             case 1: hipLaunchKernelGGL((k_res_eval<1>), grid, dim3(256), 0, st, ey); break;
             case 2: hipLaunchKernelGGL((k_res_eval<2>), grid, dim3(256), 0, st, ey); break;
             default: hipLaunchKernelGGL((k_res_eval<3>), grid, dim3(256), 0, st, ey); break;
