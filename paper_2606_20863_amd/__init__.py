@@ -352,18 +352,6 @@ def gemm_ex(A: torch.Tensor, B: torch.Tensor, C: torch.Tensor | None = None, *, 
 
 def gemm(A: torch.Tensor, B: torch.Tensor, form: str = "fp64", stream=None) -> torch.Tensor:
     """C = A B for m-double planes A (m, M, K) and B (m, K, N)."""
-    if form == "fp64" and stream is None:
-        _check_planes(A, "A")
-        _check_planes(B, "B")
-        A = A.contiguous()
-        B = B.contiguous()
-        m, M, K = A.shape
-        N = B.shape[2]
-        if B.shape[:2] != (m, K):
-            raise ValueError("shape mismatch")
-        C = torch.empty((m, M, N), dtype=torch.float64, device=A.device)
-        _check(lib().md_gemm(m, M, N, K, _ptr(A), _ptr(B), _ptr(C), _stream_handle(None)))
-        return C
     return gemm_ex(A, B, form=form, stream=stream)[0]
 
 
