@@ -798,20 +798,12 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
                round_up(M, kTile) / kRowBlock, nullptr};
     ExpSide sb{opB, hiB, loB, F, dbg ? dbg->F : nullptr, stats + 1, stats + 6, (opB.sr == 1 && opB.sk != 1) ? 1 : 0,
                round_up(N, kTile) / kRowBlock, nullptr};
-    // the exponent pass: one launch where the depth is short and the
-    // magnitude split follows (which then makes the statistics) or nobody
-    // reads them
+    // the exponent pass, with the magnitude split where a block holds its
+    // rows' depth (a forced S needs neither magnitudes nor statistics)
     const bool use_rho = o.force_S == 0 && o.s_rule == MD_S_RHO;
-    const bool exp_rows = K <= kExpRowsDepth && (use_rho || o.force_S > 0);
-    if ((e = exp_rows ? launch_exp_rows2(sa, sb, eoff, st) : launch_exp_pass2(sa, sb, stats, eoff, st)) != hipSuccess)
-        return hip_fail(e);
-    if (E_in && (e = launch_exp_set(E_in, hiA, M, eoff, E, exp_flags, st)) != hipSuccess) return hip_fail(e);
-    if (F_in && (e = launch_exp_set(F_in, hiB, N, eoff, F, exp_flags, st)) != hipSuccess) return hip_fail(e);
-
+    const int64_t nkm = (K + kKcI8 - 1) / kKcI8;
+    unsigned long long* minP = (unsigned long long*)(stats + 2);
     if (use_rho) {
-        // magnitude certificate: min_ij sum_k qA_ik qB_kj, q the 7-bit
-        // leading-word magnitudes on the shared-exponent grid
-        const int64_t nkm = (K + kKcI8 - 1) / kKcI8;
         void *qA, *qB;
         int rc = scr.get(digits_bytes(MD_FORM_INT8, M, K, 1), &qA);
         if (rc)
@@ -821,10 +813,24 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
             return rc;
         sa.q = (int8_t*)qA;
         sb.q = (int8_t*)qB;
-        if ((e = launch_split_mag2(sa, sb, eoff, nkm, st,
-                                   exp_rows ? (unsigned long long*)(stats + 2) : nullptr)) != hipSuccess)
+    }
+    const bool exp_mag = K <= kExpMagDepth && (use_rho || o.force_S > 0);
+    if ((e = exp_mag ? launch_exp_mag2(sa, sb, eoff, nkm, use_rho ? minP : nullptr, st)
+                     : launch_exp_pass2(sa, sb, stats, eoff, st)) != hipSuccess)
+        return hip_fail(e);
+    if (E_in && (e = launch_exp_set(E_in, hiA, M, eoff, E, exp_flags, st)) != hipSuccess) return hip_fail(e);
+    if (F_in && (e = launch_exp_set(F_in, hiB, N, eoff, F, exp_flags, st)) != hipSuccess) return hip_fail(e);
+
+    if (use_rho) {
+        // magnitude certificate: min_ij sum_k qA_ik qB_kj, q the 7-bit
+        // leading-word magnitudes on the shared-exponent grid
+        const ExpBlocks from{{loA, loB},
+                             {(M + kRowBlock - 1) / kRowBlock, (N + kRowBlock - 1) / kRowBlock},
+                             {sa.span_max, sb.span_max},
+                             {sa.ext, sb.ext}};
+        if (!exp_mag && (e = launch_split_mag2(sa, sb, eoff, nkm, st)) != hipSuccess)
             return hip_fail(e);
-        if ((e = launch_mag_min(qA, qB, M, N, nkm, (unsigned long long*)(stats + 2), st)) != hipSuccess)
+        if ((e = launch_mag_min(sa.q, sb.q, M, N, nkm, minP, st, exp_mag ? &from : nullptr)) != hipSuccess)
             return hip_fail(e);
     }
     Choice ch;

@@ -4,6 +4,7 @@
 #include "slice_common.h"
 #include "dotlane.h"
 #include "dotmma.h"
+#include "expstats.h"
 
 #include <climits>
 
@@ -23,8 +24,11 @@ template <int RX, int CY, int D>
 __global__ __launch_bounds__(256) void k_mag_min_short(const v4i* __restrict__ qA,
                                                        const v4i* __restrict__ qB, int64_t M,
                                                        int64_t N, int64_t nkc,
-                                                       unsigned long long* minP, int64_t y0)
+                                                       unsigned long long* minP, int64_t y0, ExpBlocks from)
 {
+    if (from.n[0] && blockIdx.x == 0 && blockIdx.y == 0 && y0 == 0)
+        for (int z = 0; z < 2; ++z)
+            exp_block_stats(from.lo[z], from.n[z], from.span_max[z], from.ext[z]);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t rb0 = ((y0 + blockIdx.y) * 2 + (wave >> 1)) * RX;
@@ -310,8 +314,11 @@ struct DispatchDot<Form, 0> {
 }  // namespace
 
 hipError_t launch_mag_min(const void* qA, const void* qB, int64_t M, int64_t N, int64_t nkc,
-                          unsigned long long* minP, hipStream_t st)
+                          unsigned long long* minP, hipStream_t st, const ExpBlocks* from)
 {
+    const ExpBlocks fb = from ? *from : ExpBlocks{};
+    if (fb.n[0] && nkc > 2048)
+        return hipErrorInvalidValue;   // launch_exp_mag2's depths are far below
     // 256 x 256 outputs per workgroup where that still gives every compute
     // unit one (4096^2 outputs and up), else 128 x 128
     const bool wide = nkc <= 2048 && ((N + 255) / 256) * ((M + 255) / 256) >= 256;
@@ -323,10 +330,10 @@ hipError_t launch_mag_min(const void* qA, const void* qB, int64_t M, int64_t N, 
         dim3 grid((unsigned)gx, (unsigned)std::min<int64_t>(ny - y0, 65535));
         if (wide)
             hipLaunchKernelGGL((k_mag_min_short<8, 8, 2>), grid, dim3(256), 0, st, (const v4i*)qA,
-                               (const v4i*)qB, M, N, nkc, minP, y0);
+                               (const v4i*)qB, M, N, nkc, minP, y0, fb);
         else if (nkc <= 2048)
             hipLaunchKernelGGL((k_mag_min_short<4, 4, 4>), grid, dim3(256), 0, st, (const v4i*)qA,
-                               (const v4i*)qB, M, N, nkc, minP, y0);
+                               (const v4i*)qB, M, N, nkc, minP, y0, fb);
         else
             hipLaunchKernelGGL(k_mag_min, grid, dim3(256), 0, st, (const v4i*)qA, (const v4i*)qB, M, N,
                                nkc, minP, y0);

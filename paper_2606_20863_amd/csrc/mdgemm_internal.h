@@ -119,17 +119,17 @@ struct ExpSide {
     int8_t* q;               // magnitude digits
 };
 hipError_t launch_exp_pass2(const ExpSide& a, const ExpSide& b, int32_t* stats, int eoff, hipStream_t st);
-hipError_t launch_split_mag2(const ExpSide& a, const ExpSide& b, int eoff, int64_t nkc, hipStream_t st,
-                             unsigned long long* minP = nullptr);
-// The exponent pass in one launch (a block takes its rows' whole depth: K up
-// to kExpRowsDepth), E and hi as launch_exp_pass2's.  It leaves no
-// statistics: launch_split_mag2 with minP makes them (a call that needs
-// none, with S forced, stops here).  lo is its working space.  A thread
-// reads K / 16 words one batch after the other: at K = 1024 the block's
-// chain of loads costs more than the two launches (1024^3: 346 -> 359 us a
-// call), at 64 they are most of the pass (64^3: see launch_split_i8).
-constexpr int64_t kExpRowsDepth = 256;
-hipError_t launch_exp_rows2(const ExpSide& a, const ExpSide& b, int eoff, hipStream_t st);
+hipError_t launch_split_mag2(const ExpSide& a, const ExpSide& b, int eoff, int64_t nkc, hipStream_t st);
+// Both in one launch, up to kExpMagDepth (where a block's threads hold their
+// rows' depth): E and hi as launch_exp_pass2's, the magnitude digits where q
+// is set, *minP (optional) set to its initial value.  The statistics come
+// from launch_mag_min with `from`; lo is the working space between them.
+// (4096 depths, 64 a thread, do not fit its registers: 4096 x 24 x 4096 486 ->
+// 633 us a call.  1024^3 quad-doubles 319 -> 311, 2048^3 double-doubles
+// forward and adjoint 3050 -> 2983.)
+constexpr int64_t kExpMagDepth = 2048;
+hipError_t launch_exp_mag2(const ExpSide& a, const ExpSide& b, int eoff, int64_t nkc, unsigned long long* minP,
+                           hipStream_t st);
 // E[r] = shared exponent + eoff (2 for the balanced INT8 digits, else 0);
 // dbgE gets the shared exponent itself; ext (optional) the largest and
 // smallest shared exponent of the rows with a nonzero leading word
@@ -172,8 +172,16 @@ hipError_t launch_split_f64(const SplitSide& a, const SplitSide& b, int m, int S
 hipError_t launch_gemm_i8(const GemmArgs& a, hipStream_t st);
 // minP[0] = min over (i < M, j < N) of sum_k qA_ik qB_kj (must start at
 // UINT64_MAX); qA, qB from launch_split_mag2, nkc depth fragments each.
+// from (optional; the operands of launch_exp_mag2): also make their spans and
+// extreme exponents
+struct ExpBlocks {
+    const int32_t* lo[2];
+    int64_t n[2];            // 16-row blocks; n[0] = 0: none
+    int32_t* span_max[2];
+    int32_t* ext[2];
+};
 hipError_t launch_mag_min(const void* qA, const void* qB, int64_t M, int64_t N, int64_t nkc,
-                          unsigned long long* minP, hipStream_t st);
+                          unsigned long long* minP, hipStream_t st, const ExpBlocks* from = nullptr);
 hipError_t launch_gemm_f64(const GemmArgs& a, hipStream_t st);
 // exact fold and rounding of every output from a.gD (one thread per entry)
 hipError_t launch_gemm_final(const GemmArgs& a, hipStream_t st);

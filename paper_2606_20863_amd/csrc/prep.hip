@@ -444,117 +444,131 @@ __global__ void k_exp_final2(ExpSide a, ExpSide b, int eoff)
         exp_final_rows(b.hi, b.lo, b.op.R, b.E, b.span_max, b.ext, b.dbgE, eoff, r);
 }
 
-// The whole exponent pass of both operands where the depth is short: a block
-// finds its 16 rows' exponents itself (no atomics, so no initial values and
-// no last pass: one launch instead of three), and leaves its span and
-// extreme exponents in lo[4 bx ..], which k_split_mag2 reduces.  Thread
-// (row, k) as in exp_partial_block.
-__global__ __launch_bounds__(256) void k_exp_rows2(ExpSide a, ExpSide b, int eoff)
+// The exponent pass and the magnitude split of both operands in one launch
+// and one reading, where a block's threads hold their rows' depth: each
+// entry's exponent and top seven bits stay in a register until the row's
+// shared exponent is known (no atomics, so no initial values and no last
+// pass).  A block takes 16 rows with 4 NW threads a row, each groups of four
+// consecutive depths (one dword of a magnitude fragment).  Rows contiguous
+// in depth: a row's threads are adjacent lanes; rows_fast: 16 rows to
+// adjacent lanes, so that every load is 128 contiguous bytes.  The block
+// leaves its span and extreme exponents in lo[4 bx ..] for launch_mag_min
+// (exp_block_stats).  q null: exponents only.
+template <int NW, int J>
+__global__ __launch_bounds__(64 * NW) void k_exp_mag2(ExpSide a, ExpSide b, int eoff, int64_t nkc,
+                                                      unsigned long long* minP)
 {
+    constexpr int G = 4 * NW;   // groups of four depths side by side
+    if (minP && blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0)
+        *minP = ~0ull;
     const ExpSide s = blockIdx.z == 0 ? a : b;
-    const int64_t r0 = (int64_t)blockIdx.x * kExpRows;
-    if (r0 >= s.op.R)
+    const int64_t rb = blockIdx.x;
+    if (rb >= s.nrb)
         return;
-    __shared__ int sh[4][kExpRows], sl[4][kExpRows];
-    const int t = threadIdx.x, wave = t >> 6;
-    const int tr = s.rows_fast ? (t & 15) : (t >> 4);
-    const int tk = s.rows_fast ? (t >> 4) : (t & 15);
-    const int64_t r = r0 + tr;
+    __shared__ int sh[NW][kExpRows], sl[NW][kExpRows], se[kExpRows];
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    const int row = s.rows_fast ? lane & 15 : t / G, g0 = s.rows_fast ? wave * 4 + (lane >> 4) : t % G;
+    const int64_t r = rb * kExpRows + row;
+    const double* p = s.op.p + min(r, s.op.R - 1) * s.op.sr;
     int h = INT_MIN, l = INT_MAX;
-    if (r < s.op.R) {
-        const double* p = s.op.p + r * s.op.sr;
-#pragma unroll 16
-        for (int64_t k = tk; k < s.op.K; k += 16) {
-            const double x = p[k * s.op.sk];
-            if (x != 0.0) {
-                const int e = frexp_exponent(x);
-                h = max(h, e);
-                l = min(l, e);
+    uint32_t pk[J * 4];   // exponent + 2048 above the top seven bits; 0 for zero
+    constexpr int JB = J < 4 ? J : 4;   // groups whose loads are in flight at once
+#pragma unroll
+    for (int j0 = 0; j0 < J; j0 += JB) {
+        double x[JB * 4];
+#pragma unroll
+        for (int j = 0; j < JB; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int64_t k = 4 * (g0 + G * (j0 + j)) + c;
+                const double v = p[min(k, s.op.K - 1) * s.op.sk];   // clamped, not branched around
+                x[4 * j + c] = r < s.op.R && k < s.op.K ? v : 0.0;
             }
+#pragma unroll
+        for (int c = 0; c < JB * 4; ++c) {
+            const uint64_t bits = (uint64_t)__double_as_longlong(x[c]) & ~(1ull << 63);
+            const bool nz = bits != 0;
+            int e = (int)(bits >> 52) - 1022;
+            uint32_t top = 64u | ((uint32_t)(bits >> 46) & 63u);
+            if (nz && e == -1022) {   // subnormal: |x| = bits 2^-1074
+                const int n = 64 - __builtin_clzll(bits);
+                e = n - 1074;
+                top = (uint32_t)(n > 7 ? bits >> (n - 7) : bits << (7 - n));
+            }
+            h = max(h, nz ? e : INT_MIN);
+            l = min(l, nz ? e : INT_MAX);
+            pk[4 * j0 + c] = nz ? (uint32_t)(e + 2048) << 8 | top : 0u;
         }
+        asm volatile("" ::: "memory");   // a batch's words do not outlive it
     }
-    // rows in lanes 16 apart of every wave, or in 16 adjacent lanes of one
-    for (int o = s.rows_fast ? 16 : 1; o < (s.rows_fast ? 64 : 16); o <<= 1) {
+    const int o0 = s.rows_fast ? 16 : 1, o1 = s.rows_fast ? 64 : G;
+    for (int o = o0; o < o1; o <<= 1) {
         h = max(h, __shfl_xor(h, o));
         l = min(l, __shfl_xor(l, o));
     }
-    if (s.rows_fast) {
-        if ((t & 63) < 16) {
-            sh[wave][tr] = h;
-            sl[wave][tr] = l;
-        }
-    } else if (tk == 0) {
+    if (s.rows_fast ? lane < 16 : g0 == 0) {
+        // rows of adjacent lanes are whole: every wave's slot the same
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            sh[w][tr] = h;
-            sl[w][tr] = l;
+        for (int w = 0; w < NW; ++w)
+            if (!s.rows_fast || w == wave) {
+                sh[w][row] = h;
+                sl[w][row] = l;
+            }
+    }
+    __syncthreads();
+    if (t < kExpRows) {
+        h = INT_MIN;
+        l = INT_MAX;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            h = max(h, sh[w][t]);
+            l = min(l, sl[w][t]);
+        }
+        const int e = h == INT_MIN ? 0 : h;
+        int span = h == INT_MIN ? 0 : h - l, emax = h, emin = h == INT_MIN ? INT_MAX : h;
+        se[t] = e;
+        const int64_t rt = rb * kExpRows + t;
+        if (rt < s.op.R) {
+            s.hi[rt] = h;
+            s.E[rt] = e + eoff;
+            if (s.dbgE)
+                s.dbgE[rt] = e;
+        }
+        for (int o = 1; o < kExpRows; o <<= 1) {
+            span = max(span, __shfl_xor(span, o));
+            emax = max(emax, __shfl_xor(emax, o));
+            emin = min(emin, __shfl_xor(emin, o));
+        }
+        if (t == 0 && rt < s.op.R) {
+            int32_t* q = s.lo + 4 * rb;
+            q[0] = span;
+            q[1] = emax;
+            q[2] = emin;
         }
     }
-    __syncthreads();
-    if (t >= kExpRows)
+    if (!s.q)
         return;
-    h = max(max(sh[0][t], sh[1][t]), max(sh[2][t], sh[3][t]));
-    l = min(min(sl[0][t], sl[1][t]), min(sl[2][t], sl[3][t]));
-    const int e = h == INT_MIN ? 0 : h;
-    int span = h == INT_MIN ? 0 : h - l, emax = h, emin = h == INT_MIN ? INT_MAX : h;
-    if (r0 + t < s.op.R) {
-        s.hi[r0 + t] = h;
-        s.E[r0 + t] = e + eoff;
-        if (s.dbgE)
-            s.dbgE[r0 + t] = e;
-    }
-    for (int o = 1; o < 16; o <<= 1) {
-        span = max(span, __shfl_xor(span, o));
-        emax = max(emax, __shfl_xor(emax, o));
-        emin = min(emin, __shfl_xor(emin, o));
-    }
-    if (t == 0) {
-        int32_t* q = s.lo + 4 * (int64_t)blockIdx.x;
-        q[0] = span;
-        q[1] = emax;
-        q[2] = emin;
-    }
-}
-
-// The statistics of one side from k_exp_rows2's blocks.
-__device__ __forceinline__ void exp_rows_stats(const ExpSide& s)
-{
-    __shared__ int red[3][4];
-    const int64_t n = (s.op.R + kExpRows - 1) / kExpRows;
-    int span = 0, emax = INT_MIN, emin = INT_MAX;
-    for (int64_t b = threadIdx.x; b < n; b += 256) {
-        span = max(span, s.lo[4 * b]);
-        emax = max(emax, s.lo[4 * b + 1]);
-        emin = min(emin, s.lo[4 * b + 2]);
-    }
-    for (int o = 1; o < 64; o <<= 1) {
-        span = max(span, __shfl_xor(span, o));
-        emax = max(emax, __shfl_xor(emax, o));
-        emin = min(emin, __shfl_xor(emin, o));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        red[0][threadIdx.x >> 6] = span;
-        red[1][threadIdx.x >> 6] = emax;
-        red[2][threadIdx.x >> 6] = emin;
-    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        *s.span_max = max(max(red[0][0], red[0][1]), max(red[0][2], red[0][3]));
-        s.ext[0] = max(max(red[1][0], red[1][1]), max(red[1][2], red[1][3]));
-        s.ext[1] = min(min(red[2][0], red[2][1]), min(red[2][2], red[2][3]));
+    const int er = se[row];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int64_t k = 4 * (g0 + G * j);
+        uint32_t d = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            // floor(|x| 2^(7 - er)): the top seven bits moved down
+            const uint32_t v = pk[4 * j + c];
+            d |= ((v & 127u) >> min(er + 2048 - (int)(v >> 8), 31)) << (8 * c);
+        }
+        const int64_t kc = k >> 6;
+        const int kk = (int)(k & 63);
+        if (kc < nkc)
+            reinterpret_cast<uint32_t*>(s.q)[(rb * nkc + kc) * 256 + (row + 16 * (kk >> 4)) * 4 + ((kk & 15) >> 2)] = d;
     }
 }
 
-// minP (after k_exp_rows2, else null): the smallest magnitude product's
-// initial value, and the statistics, set here
-__global__ __launch_bounds__(256) void k_split_mag2(ExpSide a, ExpSide b, int eoff, int64_t nkc, int64_t rb0,
-                                                    unsigned long long* minP)
+__global__ __launch_bounds__(256) void k_split_mag2(ExpSide a, ExpSide b, int eoff, int64_t nkc, int64_t rb0)
 {
-    if (minP && blockIdx.x == 0 && blockIdx.y == 0 && rb0 == 0) {
-        exp_rows_stats(blockIdx.z == 0 ? a : b);
-        if (blockIdx.z == 0 && threadIdx.x == 0)
-            *minP = ~0ull;
-    }
     const int64_t rb = rb0 + blockIdx.y;
     if (blockIdx.z == 0) {
         if (rb < a.nrb)
@@ -799,24 +813,35 @@ hipError_t launch_exp_pass2(const ExpSide& a, const ExpSide& b, int32_t* stats, 
     return hipGetLastError();
 }
 
-hipError_t launch_exp_rows2(const ExpSide& a, const ExpSide& b, int eoff, hipStream_t st)
+hipError_t launch_exp_mag2(const ExpSide& a, const ExpSide& b, int eoff, int64_t nkc, unsigned long long* minP,
+                           hipStream_t st)
 {
-    const int64_t gx = (std::max(a.op.R, b.op.R) + kExpRows - 1) / kExpRows;
-    if (gx < 1 || gx > 0x7fffffff)
+    const int64_t nrb = std::max(a.nrb, b.nrb), K = a.op.K;
+    if (K < 1 || K != b.op.K || K > kExpMagDepth || nrb < 1 || nrb > 0x7fffffff)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_exp_rows2, dim3((unsigned)gx, 1, 2), dim3(256), 0, st, a, b, eoff);
+    const dim3 grid((unsigned)nrb, 1, 2);
+    // 4 waves a block up to 256 depths, else 16
+    if (K <= 64)
+        hipLaunchKernelGGL((k_exp_mag2<4, 1>), grid, dim3(256), 0, st, a, b, eoff, nkc, minP);
+    else if (K <= 256)
+        hipLaunchKernelGGL((k_exp_mag2<4, 4>), grid, dim3(256), 0, st, a, b, eoff, nkc, minP);
+    else if (K <= 512)
+        hipLaunchKernelGGL((k_exp_mag2<16, 2>), grid, dim3(1024), 0, st, a, b, eoff, nkc, minP);
+    else if (K <= 1024)
+        hipLaunchKernelGGL((k_exp_mag2<16, 4>), grid, dim3(1024), 0, st, a, b, eoff, nkc, minP);
+    else
+        hipLaunchKernelGGL((k_exp_mag2<16, 8>), grid, dim3(1024), 0, st, a, b, eoff, nkc, minP);
     return hipGetLastError();
 }
 
-hipError_t launch_split_mag2(const ExpSide& a, const ExpSide& b, int eoff, int64_t nkc, hipStream_t st,
-                             unsigned long long* minP)
+hipError_t launch_split_mag2(const ExpSide& a, const ExpSide& b, int eoff, int64_t nkc, hipStream_t st)
 {
     if (nkc > 0x7fffffff)
         return hipErrorInvalidValue;
     const int64_t nrb = std::max(a.nrb, b.nrb);
     for (int64_t y0 = 0; y0 < nrb; y0 += kMaxGridY) {
         const dim3 grid((unsigned)nkc, (unsigned)std::min<int64_t>(nrb - y0, kMaxGridY), 2);
-        hipLaunchKernelGGL(k_split_mag2, grid, dim3(256), 0, st, a, b, eoff, nkc, y0, minP);
+        hipLaunchKernelGGL(k_split_mag2, grid, dim3(256), 0, st, a, b, eoff, nkc, y0);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             return e;
@@ -968,8 +993,7 @@ hipError_t split_place_sc(const SplitSide& a, const SplitSide& b, int S, int64_t
 
 // Both operands in one launch (blockIdx.z) where they are of like size: a
 // small product is bound by its launches (64^3 double-doubles, the slice
-// rule's call: 70 -> 39 us with this and the one-launch exponent pass, six
-// kernels instead of nine).  The grid covers the larger one,
+// rule's call: 70 -> 39 us with this and a one-launch exponent pass).  The grid covers the larger one,
 // so operands of unlike size get a launch each.
 template <class Launch>
 hipError_t split_sides(const SplitSide& a, const SplitSide& b, Launch launch)
