@@ -389,6 +389,12 @@ int md_choose_params(int form, int64_t K, int T, int G, int *beta, int *S, int *
  * workspace that lets a call allocate nothing). */
 size_t md_gemm_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S);
 
+/* INT8 matrix products of depth K by which md_gemm_ex contracts these sizes,
+ * S and beta where it takes the residues of the digits (csrc/resid.h; with
+ * scratch of md_gemm_workspace_size bytes), 0 where it multiplies the slices
+ * themselves (S (S + 1) / 2 products).  Host only. */
+int md_gemm_planes(int form, int64_t M, int64_t N, int64_t K, int S, int beta);
+
 /* The same (the name of earlier versions). */
 size_t md_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S);
 

@@ -130,6 +130,8 @@ def lib():
     L.md_choose_params.restype = i32
     L.md_gemm_workspace_size.argtypes = [i32, i64, i64, i64, i32]
     L.md_gemm_workspace_size.restype = ctypes.c_size_t
+    L.md_gemm_planes.argtypes = [i32, i64, i64, i64, i32, i32]
+    L.md_gemm_planes.restype = i32
     L.md_workspace_size.argtypes = [i32, i64, i64, i64, i32]
     L.md_workspace_size.restype = ctypes.c_size_t
     L.md_dot_workspace_size.argtypes = [i32, i64, i64, i32]

@@ -660,6 +660,15 @@ size_t md_gemm_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S)
     return bytes;
 }
 
+int md_gemm_planes(int form, int64_t M, int64_t N, int64_t K, int S, int beta)
+{
+    ResPlan rp;
+    ResPanels pn;
+    if (form < MD_FORM_FP64 || form > MD_FORM_INT8_BAL || M < 1 || N < 1 || K < 1 || S < 1 || beta < 1)
+        return 0;
+    return take_residues(form, S, beta, M, N, K, true, rp, pn) ? rp.planes() : 0;
+}
+
 size_t md_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S)
 {
     return md_gemm_workspace_size(form, M, N, K, S);
@@ -859,8 +868,11 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
         ResPanels pn;
         void *dA = nullptr, *dB = nullptr, *work = nullptr;
         if (!dbg && take_residues(o.form, S, beta, M, N, K, duo, rp, pn)) {
-            const size_t bA = digits_bytes(MD_FORM_INT8, M, K, rp.SB), bB = digits_bytes(MD_FORM_INT8, N, K, rp.SB);
-            if (scr.holds(bA + bB + pn.bytes + 512) && !scr.get(bA, &dA) && !scr.get(bB, &dB) && !scr.get(pn.bytes, &work)) {
+            const bool cuts = res_cuts(rp, m);   // the evaluation cuts the digits itself: no digit planes
+            const size_t bA = cuts ? 0 : digits_bytes(MD_FORM_INT8, M, K, rp.SB);
+            const size_t bB = cuts ? 0 : digits_bytes(MD_FORM_INT8, N, K, rp.SB);
+            if (scr.holds(bA + bB + pn.bytes + 512) && (cuts || (!scr.get(bA, &dA) && !scr.get(bB, &dB))) &&
+                !scr.get(pn.bytes, &work)) {
                 GemmArgs ga;
                 memset(&ga, 0, sizeof(ga));
                 ga.A = dA;
@@ -883,13 +895,16 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
                     ga.fixNL = fx->nlimb;
                 }
                 const SplitSide pa{opA, E, Mp / kRowBlock, dA, nullptr}, pb{opB, F, Np / kRowBlock, dB, nullptr};
-                e = is_i8(o.form) ? launch_split_i8(pa, pb, m, S, ga.nkc, o.form == MD_FORM_INT8_BAL, st)
-                                  : launch_split_f64b(pa, pb, m, S, beta, rp.nb, ga.nkc, st);
+                if (cuts)
+                    e = hipSuccess;
+                else
+                    e = is_i8(o.form) ? launch_split_i8(pa, pb, m, S, ga.nkc, o.form == MD_FORM_INT8_BAL, st)
+                                      : launch_split_f64b(pa, pb, m, S, beta, rp.nb, ga.nkc, st);
                 if (e != hipSuccess)
                     return hip_fail(e);
                 if (o.ev_gemm_begin && (e = hipEventRecord((hipEvent_t)o.ev_gemm_begin, st)) != hipSuccess)
                     return hip_fail(e);
-                if ((e = launch_resid(rp, pn, ga, (char*)work, st)) != hipSuccess)
+                if ((e = launch_resid(rp, pn, ga, pa, pb, (char*)work, st)) != hipSuccess)
                     return hip_fail(e);
                 if (o.ev_gemm_end && (e = hipEventRecord((hipEvent_t)o.ev_gemm_end, st)) != hipSuccess)
                     return hip_fail(e);

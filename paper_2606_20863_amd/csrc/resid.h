@@ -71,9 +71,13 @@ struct ResPanels {
 bool res_panels(const ResPlan& r, int64_t M, int64_t N, int64_t K, ResPanels& p);
 
 // Fixed-point and rounded outputs as GemmArgs' (C, ldc, psc, E, F, M, N, m,
-// fixX, fixScale, fixNL, ncol, beta, S); dA, dB: digit planes in INT8
-// fragment order (launch_split_i8, or launch_split_f64b for the FP64 form)
-hipError_t launch_resid(const ResPlan& r, const ResPanels& p, const GemmArgs& a, char* scratch, hipStream_t st);
+// fixX, fixScale, fixNL, ncol, beta, S).  Where res_cuts the digits are cut
+// from the operands' words (A, B: op and E) by the evaluation itself; else
+// a.A and a.B are digit planes in INT8 fragment order (launch_split_i8, or
+// launch_split_f64b for the FP64 form).
+bool res_cuts(const ResPlan& r, int m);
+hipError_t launch_resid(const ResPlan& r, const ResPanels& p, const GemmArgs& a, const SplitSide& A, const SplitSide& B,
+                        char* scratch, hipStream_t st);
 
 // FP64 digits of beta bits as byte planes: digit s is sum_k c_k 256^k with
 // c_k in [-128, 127], byte k in plane s nb + k, INT8 fragment order

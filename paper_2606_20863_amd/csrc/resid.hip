@@ -1,7 +1,9 @@
 // The residue contraction (resid.h): tables, evaluation, the batched INT8
 // products and the interpolation with the exact fold and rounding.
 #include "resid.h"
+#include "ldslimbs.h"
 #include "renorm.h"
+#include "split.h"
 
 #include <algorithm>
 #include <cmath>
@@ -249,6 +251,33 @@ struct ResEvalArgs {
     int SB, planes, KD;
 };
 
+// Digits of one row as evaluation operands: T[kt][e] holds digits 4 PL kt +
+// PL q .. + PL - 1 of depth e, transposed from 16 depths of one digit at a
+// time; digit(s) gives those (16 bytes), zeros from the last digit on.
+template <int KT, class F>
+__device__ __forceinline__ void res_operands(F&& digit, int q, uint32_t (&T)[KT ? KT : 1][16][KT ? 4 : 2])
+{
+    constexpr int KN = KT ? KT : 1, PL = KT ? 16 : 8;   // operands, digits per lane and operand
+#pragma unroll
+    for (int kt = 0; kt < KN; ++kt) {
+        v4i D[PL];
+#pragma unroll
+        for (int i = 0; i < PL; ++i)
+            D[i] = digit(4 * PL * kt + PL * q + i);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int g = 0; g < PL / 4; ++g) {
+                uint32_t w0 = D[4 * g][c], w1 = D[4 * g + 1][c], w2 = D[4 * g + 2][c], w3 = D[4 * g + 3][c];
+                transpose4(w0, w1, w2, w3);
+                T[kt][4 * c][g] = w0;
+                T[kt][4 * c + 1][g] = w1;
+                T[kt][4 * c + 2][g] = w2;
+                T[kt][4 * c + 3][g] = w3;
+            }
+    }
+}
+
 // Residues of one 16 x 64 digit fragment (all planes).  The evaluation is a
 // matrix product, weights [planes x digits] by digits [digits x entries]:
 // wave w takes the 16 rows at depths 16 w .. 16 w + 15 of the fragment (lane
@@ -263,38 +292,12 @@ struct ResEvalArgs {
 // four waves per SIMD instead of three (4096^2 entries, 27 digits to 164
 // planes: 735 -> 628 us, 5.1 TB/s).
 template <int KT>
-__global__ __launch_bounds__(256) void k_res_eval(ResEvalArgs a)
+__device__ __forceinline__ void res_planes(const uint32_t (&T)[KT ? KT : 1][16][KT ? 4 : 2], const int8_t* weights,
+                                           const float2* pc, int KD, int planes, char* dst, int64_t plane, int n, int q)
 {
-    constexpr int KN = KT ? KT : 1, PL = KT ? 16 : 8;   // operands, digits per lane and operand
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 15, q = lane >> 4;
-    const int64_t rb = blockIdx.y;
-    const int kc = blockIdx.x;
-    const char* src = a.dig + (rb * a.nkc + kc) * ((int64_t)a.SB * 1024) + (wave * 16 + n) * 16;
-    uint32_t T[KN][16][PL / 4];   // T[kt][e]: digits 4 PL kt + PL q .. + PL - 1 of depth e
-#pragma unroll
-    for (int kt = 0; kt < KN; ++kt) {
-        v4i D[PL];
-#pragma unroll
-        for (int i = 0; i < PL; ++i) {
-            const int s = 4 * PL * kt + PL * q + i;
-            D[i] = s < a.SB && kc < a.nkc ? *(const v4i*)(src + (int64_t)s * 1024) : v4i{0, 0, 0, 0};
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int g = 0; g < PL / 4; ++g) {
-                uint32_t w0 = D[4 * g][c], w1 = D[4 * g + 1][c], w2 = D[4 * g + 2][c], w3 = D[4 * g + 3][c];
-                transpose4(w0, w1, w2, w3);
-                T[kt][4 * c][g] = w0;
-                T[kt][4 * c + 1][g] = w1;
-                T[kt][4 * c + 2][g] = w2;
-                T[kt][4 * c + 3][g] = w3;
-            }
-    }
-    char* dst = a.out + (rb * a.nkr + kc) * 1024 + (wave * 16 + n) * 16;
-    for (int t = 0; t < a.planes; t += 16) {
-        const int8_t* V = a.V + (int64_t)(t + n) * a.KD + PL * q;
+    constexpr int KN = KT ? KT : 1, PL = KT ? 16 : 8;
+    for (int t = 0; t < planes; t += 16) {
+        const int8_t* V = weights + (int64_t)(t + n) * KD + PL * q;
         int64_t vh = 0;
         v4i vf[KN];
         if constexpr (KT == 0) {
@@ -308,7 +311,7 @@ __global__ __launch_bounds__(256) void k_res_eval(ResEvalArgs a)
         int negp[4];
 #pragma unroll
         for (int o = 0; o < 4; ++o) {
-            const float2 c = a.pc[t + 4 * q + o];
+            const float2 c = pc[t + 4 * q + o];
             inv[o] = c.x;
             negp[o] = -(int)c.y;
         }
@@ -339,9 +342,152 @@ __global__ __launch_bounds__(256) void k_res_eval(ResEvalArgs a)
         }
 #pragma unroll
         for (int o = 0; o < 4; ++o)
-            if (t + 4 * q + o < a.planes)
-                *(v4i*)(dst + (int64_t)(t + 4 * q + o) * a.plane) = w[o];
+            if (t + 4 * q + o < planes)
+                *(v4i*)(dst + (int64_t)(t + 4 * q + o) * plane) = w[o];
     }
+}
+
+template <int KT>
+__global__ __launch_bounds__(256) void k_res_eval(ResEvalArgs a)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = lane & 15, q = lane >> 4;
+    const int64_t rb = blockIdx.y;
+    const int kc = blockIdx.x;
+    const char* src = a.dig + (rb * a.nkc + kc) * ((int64_t)a.SB * 1024) + (wave * 16 + n) * 16;
+    uint32_t T[KT ? KT : 1][16][KT ? 4 : 2];
+    res_operands<KT>(
+        [&](int s) { return s < a.SB && kc < a.nkc ? *(const v4i*)(src + (int64_t)s * 1024) : v4i{0, 0, 0, 0}; }, q, T);
+    res_planes<KT>(T, a.V, a.pc, a.KD, a.planes, a.out + (rb * a.nkr + kc) * 1024 + (wave * 16 + n) * 16, a.plane, n, q);
+}
+
+constexpr int kCutF64 = 0, kCutSm = 1, kCutBal = 2;   // the digit forms
+
+// One or both operands (z) of a product: words in, residue planes out.
+struct ResCutArgs {
+    SplitSide s[2];       // op from the panel's first row, E, nrb; out: residue planes
+    const int8_t* V[2];
+    int64_t plane[2];     // bytes of one residue plane
+    const float2* pc;
+    int64_t rb0;          // row block of blockIdx.y = 0
+    int S, beta, nb, SB, planes, KD;
+};
+
+// The split and the evaluation of up to 32 digits of 1, 2 or 4 words in one
+// kernel: a workgroup cuts the digits of one fragment (16 rows x 64 depths,
+// four entries a thread, as the split kernels do: word placement for the
+// INT8 forms, byte planes of the FP64 digits) into LDS in fragment order and
+// evaluates them from there, so the digits are neither written to memory nor
+// read back.  Bound by its stores (and the cut's integer instructions under
+// them): 32 KB of LDS and 124 registers, four waves per SIMD.  Both operands,
+// the split and two evaluations before against this kernel: 4096^2 quad-
+// doubles, 164 planes, 1688 -> 1482 us (4.5 TB/s); 1000 x 1200 x 1100 in
+// FP64 digits 163 -> 130; 2048^2 double-doubles in FP64 digits 237 -> 181.
+// More digits or words stay with the split and k_res_eval: their LDS would
+// leave one or two workgroups per compute unit.  FORM: kCut*.
+template <int MW, int FORM>
+__global__ __launch_bounds__(256) void k_res_cut(ResCutArgs a)
+{
+    constexpr int SC = 32;
+    constexpr bool BAL = FORM == kCutBal;
+    // the digits; before them, in the same place, the entries' limbs
+    __shared__ __attribute__((aligned(16))) uint32_t dig[SC * 256];
+    const int z = blockIdx.z, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const SplitSide sd = z ? a.s[1] : a.s[0];
+    const int64_t rb = a.rb0 + blockIdx.y;
+    if (rb >= sd.nrb)
+        return;   // the whole workgroup
+    const Operand op = sd.op;
+    const int kc = blockIdx.x;
+    const int64_t r = rb * 16 + (t >> 2 & 15);
+    const int64_t kbase = (int64_t)kc * kKcI8 + 16 * wave + 4 * (t & 3);
+    const bool row_ok = r < op.R;
+    const int Er = row_ok ? sd.E[r] : 0;
+    double x[4][MW];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const bool ok = row_ok && kbase + q < op.K;
+#pragma unroll
+        for (int w = 0; w < MW; ++w)
+            x[q][w] = ok ? op.p[w * op.ps + r * op.sr + (kbase + q) * op.sk] : 0.0;
+    }
+    if constexpr (FORM == kCutF64) {
+        uint64_t mant[4][MW];
+        int sh0[4][MW];
+        bool neg[4][MW];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int w = 0; w < MW; ++w) {
+                int ex;
+                neg[q][w] = decode(x[q][w], mant[q][w], ex);
+                sh0[q][w] = ex - Er;
+            }
+        const int D = 63 / a.beta, W = D * a.beta, nl = (a.S + D - 1) / D;
+        const uint64_t wmask = (1ull << W) - 1, dmask = (1ull << a.beta) - 1;
+        for (int j = 0; j < nl; ++j) {
+            uint64_t P[4], N[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                limb_pair<MW>(mant[q], sh0[q], neg[q], W * (j + 1), wmask, P[q], N[q]);
+            for (int i = 0; i < D && D * j + i < a.S; ++i) {
+                const int rs = W - a.beta * (i + 1);
+                uint32_t u[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    u[q] = (uint32_t)((int)((P[q] >> rs) & dmask) - (int)((N[q] >> rs) & dmask)) + 0x80808080u;
+                for (int k = 0; k < a.nb; ++k) {
+                    uint32_t packed = 0;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        packed |= (((u[q] >> (8 * k)) & 0xffu) ^ 0x80u) << (8 * q);
+                    dig[((D * j + i) * a.nb + k) * 256 + t] = packed;
+                }
+            }
+        }
+    } else {
+        constexpr int bits = BAL ? 8 : 7, NS = store_limbs<SC, BAL>();
+        static_assert(NS * 4 * 64 * 8 <= SC * 1024, "the limbs fit below the digits");
+        const int kn = Er + 1075 - bits * a.S, pad = bits * (SC - a.S);
+        LdsLimbs Ls{reinterpret_cast<uint64_t*>(dig) + wave * NS * 64 + lane};
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+            Ls.col[i * 64] = 0;
+        uint32_t xs[SC];
+#pragma unroll
+        for (int s = 0; s < SC; ++s)
+            xs[s] = 0;
+        unroll<4>([&](auto QQ) {
+            constexpr int q = decltype(QQ)::value;
+            if constexpr (BAL)
+                digits_bal<q, MW, SC>(x[q], kn, pad, xs, Ls);
+            else
+                digits_sm<q, MW, SC>(x[q], kn, pad, xs, Ls);
+        });
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < SC; ++s)
+            if (s < a.S)
+                dig[s * 256 + t] = BAL ? xs[s] ^ 0x80808080u : xs[s];
+    }
+    __syncthreads();
+    const int n = lane & 15, q = lane >> 4;
+    const uint32_t* src = dig + (wave * 16 + n) * 4;
+    uint32_t T[1][16][2];
+    res_operands<0>([&](int s) { return s < a.SB ? *(const v4i*)(src + s * 256) : v4i{0, 0, 0, 0}; }, q, T);
+    res_planes<0>(T, z ? a.V[1] : a.V[0], a.pc, a.KD, a.planes,
+                  (char*)sd.out + (rb * gridDim.x + kc) * 1024 + (wave * 16 + n) * 16, z ? a.plane[1] : a.plane[0], n, q);
+}
+
+template <int MW>
+hipError_t launch_res_cut(const ResCutArgs& a, int form, dim3 grid, hipStream_t st)
+{
+    switch (form) {
+    case kCutF64: hipLaunchKernelGGL((k_res_cut<MW, kCutF64>), grid, dim3(256), 0, st, a); break;
+    case kCutSm: hipLaunchKernelGGL((k_res_cut<MW, kCutSm>), grid, dim3(256), 0, st, a); break;
+    default: hipLaunchKernelGGL((k_res_cut<MW, kCutBal>), grid, dim3(256), 0, st, a); break;
+    }
+    return hipGetLastError();
 }
 
 struct ResGemmArgs {
@@ -925,7 +1071,10 @@ void res_layout(const ResPlan& r, int64_t mr, int64_t nc, int nchunk, int64_t K,
     l.nbB = (nc + 15) / 16;
     l.psA = l.nbA * 16 * Kp;
     l.psB = l.nbB * 16 * Kp;
-    l.psR = l.nbA * l.nbB * 256;
+    // the interpolation reads every point's plane at the same place: an odd
+    // number of 256-byte steps between planes spreads those reads over the
+    // memory channels (4096^2 outputs, 150 planes of 2^24 bytes: 1035 -> 945 us)
+    l.psR = l.nbA * l.nbB * 256 + 1280;
     l.t.KD = 64 * r.kt();
     l.t.pl16 = (r.planes() + 15) / 16 * 16;
     l.t.Lp = (r.L + 15) / 16 * 16;
@@ -1004,38 +1153,46 @@ bool res_plan(bool balanced, bool fp64, int S, int beta, int64_t K, ResPlan& r)
 
 // Expected microseconds of the residue contraction and of the slice products
 // for one product, and the line between them.  Fitted to both paths' times
-// on one MI355X over m = 1 .. 16, the three forms, cubes from 128 to 2048,
+// on one MI355X over m = 1 .. 16, the three forms, cubes from 64 to 3072,
 // 4096 x 256 x 1024, 256 x 256 x 4096, 2048 x 2048 x 256, 1024 x 1024 x 4096
 // and 4096 x 64 x 4096 (within about 15% from 100 us up).
 //
 // Residues: 256 x 256 tiles of all planes in rounds of one per compute unit,
-// 0.9 us per 64 depths and 3 us of reduction each; the residues themselves
-// 3.4e6 per us; the interpolation by its matrix products and the rounding;
-// fixed costs that grow with the planes (the evaluation's loop over them is
-// serial).  Slice products: the INT8 kernels' 64 x 32 tiles in rounds,
+// 0.85 us per 64 depths and 7 us of reduction each (0.9 and 3 from 33 digits
+// on); cutting and evaluating up to 32 digits 5.3e6 bytes of words and
+// residues per us, evaluating more 3.4e6 residues per us; the interpolation
+// by its matrix products and the rounding; fixed costs that grow with the
+// planes (the evaluation's loop over them is serial).  Up to 32 digits it is
+// within 10% of the times measured over m = 1, 2 and 4, cubes from 64 to
+// 3072 and nine oblong sizes.  Slice products: the INT8 kernels' 64 x 32 tiles in rounds,
 // S (S+1) matrix instructions per 64 depths; the FP64 kernel at 62 TFLOP/s,
 // or a tile's serial depth where tiles are few.
 //
-// So FP64 digits change over at about 512^3 double-doubles (126 us against
-// 100) and below 128^3 quad-doubles (115 against 90); INT8 octo-doubles at
-// about 256^3 (181 against 168), hexa-doubles at 128^3, quad-doubles at
-// about 2048^3 (2129 against 1993; 4096^3: 15.9 ms against 12.4), double-
-// doubles never.
+// So FP64 digits change over below 384^3 doubles and double-doubles (57 us
+// against 47 and 93 against 65) and below 128^3 quad-doubles (115 against
+// 90); INT8 octo-doubles at about 256^3 (181 against 168), hexa-doubles at
+// 128^3, quad-doubles at about 1536^3 (27 balanced digits: 952 against 921;
+// 1024^3: 295 against 396; 3072^3: 6624 against 5588), double-doubles never.
 bool res_pays(const ResPlan& r, int64_t M, int64_t N, int64_t K, bool duo, double tri_us)
 {
     const double dM = (double)M, dN = (double)N, dK = (double)K, dS = r.S;
     const double steps = (double)res_steps(K), planes = r.planes();
     const double T = std::ceil(dM / 256) * std::ceil(dN / 256);
     const double words = r.beta * r.S / 53.0;
-    const double residues = 60 + 0.25 * r.N + 0.18 * planes + std::ceil(T * planes / kResGroups) * (steps * 0.9 + 3) +
-                            (dM + dN) * steps * 64 * planes / 3.4e6 +
-                            dM * dN * 1e-6 *
-                                (12 + 4.0 * r.P * ((r.L + 15) / 16) * ((r.N + 31) / 32) + 0.6 * words * res_limbs(r, K));
+    const double rounds = std::ceil(T * planes / kResGroups);
+    const double residues =
+        r.SB <= 32 ? 25 + 0.07 * planes + rounds * (steps * 0.85 + 6.7) +
+                         (dM + dN) * steps * 64 * (planes + 8 * words) / 5.3e6 +
+                         dM * dN * 1e-6 * (21 + 0.45 * words * res_limbs(r, K))
+                   : 60 + 0.25 * r.N + 0.18 * planes + rounds * (steps * 0.9 + 3) +
+                         (dM + dN) * steps * 64 * planes / 3.4e6 +
+                         dM * dN * 1e-6 *
+                             (12 + 4.0 * r.P * ((r.L + 15) / 16) * ((r.N + 31) / 32) + 0.6 * words * res_limbs(r, K));
     double slices;
     if (r.nb) {
-        slices = 40 + std::max(dM * dN * dK * dS * (dS + 1) / 62e6, 0.0045 * dK * dS * (dS + 1));
+        slices = std::min(40.0, 18 + 2.4 * dS) + std::max(dM * dN * dK * dS * (dS + 1) / 62e6, 0.0045 * dK * dS * (dS + 1));
     } else if (tri_us > 0) {
-        slices = 30 + tri_us;
+        slices = 8 + 1.03 * tri_us;
     } else {
         const double per = duo && r.S <= kDuoMax ? 0.0113 : 0.0134;
         slices = 30 + std::ceil(std::ceil(dM / 64) * std::ceil(dN / 32) / 256) *
@@ -1063,7 +1220,7 @@ bool res_panels(const ResPlan& r, int64_t M, int64_t N, int64_t K, ResPanels& p)
         }
         res_layout(r, p.mr, p.nc, p.nchunk, K, nullptr, l);
         // the interpolation reaches 32 planes with 32-bit offsets
-        if (l.total <= kLimit && l.psR <= (INT64_C(1) << 27) &&
+        if (l.total <= kLimit && l.nbA * l.nbB * 256 <= (INT64_C(1) << 27) &&
             T * (r.npp() + p.nchunk) <= 0x7fffffff) {
             p.bytes = l.total;
             return true;
@@ -1075,7 +1232,10 @@ bool res_panels(const ResPlan& r, int64_t M, int64_t N, int64_t K, ResPanels& p)
     }
 }
 
-hipError_t launch_resid(const ResPlan& r, const ResPanels& pn, const GemmArgs& g, char* scratch, hipStream_t st)
+bool res_cuts(const ResPlan& r, int m) { return m <= 4 && r.SB <= 32; }
+
+hipError_t launch_resid(const ResPlan& r, const ResPanels& pn, const GemmArgs& g, const SplitSide& sideA,
+                        const SplitSide& sideB, char* scratch, hipStream_t st)
 {
     const int64_t K = g.nkc * kKcI8, nkr = res_steps(K);
     ResLayout l;
@@ -1137,18 +1297,63 @@ hipError_t launch_resid(const ResPlan& r, const ResPanels& pn, const GemmArgs& g
         }
         return hipSuccess;
     };
+    // residues of A's rows r0 .. and / or of B's columns c0 .. from the words
+    auto cut = [&](int64_t r0, int64_t mr, int64_t c0, int64_t nc, char* outA, char* outB) {
+        ResCutArgs ca;
+        auto side = [&](int k, const SplitSide& x, int64_t at, int64_t rows, char* out, const int8_t* V, int64_t plane) {
+            ca.s[k] = x;
+            ca.s[k].op.p += at * x.op.sr;
+            ca.s[k].op.R -= at;
+            ca.s[k].E += at;
+            ca.s[k].nrb = (rows + 15) / 16;
+            ca.s[k].out = out;
+            ca.V[k] = V;
+            ca.plane[k] = plane;
+        };
+        int n = 0;
+        if (outA)
+            side(n++, sideA, r0, mr, outA, l.t.VA, l.psA);
+        if (outB)
+            side(n++, sideB, c0, nc, outB, l.t.VB, l.psB);
+        if (n == 1)
+            ca.s[1] = ca.s[0], ca.V[1] = ca.V[0], ca.plane[1] = ca.plane[0];   // not read
+        ca.pc = l.t.pc;
+        ca.S = r.S;
+        ca.beta = r.beta;
+        ca.nb = r.nb;
+        ca.SB = r.SB;
+        ca.planes = r.planes();
+        ca.KD = l.t.KD;
+        const int form = r.nb ? kCutF64 : r.beta == 7 ? kCutSm : kCutBal;
+        const int64_t nrb = std::max(ca.s[0].nrb, ca.s[1].nrb);
+        for (ca.rb0 = 0; ca.rb0 < nrb; ca.rb0 += 65535) {
+            const dim3 grid((unsigned)nkr, (unsigned)std::min<int64_t>(nrb - ca.rb0, 65535), n);
+            const hipError_t ce = g.m == 1   ? launch_res_cut<1>(ca, form, grid, st)
+                                  : g.m == 2 ? launch_res_cut<2>(ca, form, grid, st)
+                                             : launch_res_cut<4>(ca, form, grid, st);
+            if (ce != hipSuccess)
+                return ce;
+        }
+        return hipSuccess;
+    };
+    const bool cuts = res_cuts(r, g.m);
     const int64_t row_bytes = g.nkc * (int64_t)r.SB * 64;   // digit bytes of one row (64 depths x SB per chunk)
     char* pA = scratch + l.A;
     char* pB = scratch + l.B;
     for (int64_t r0 = 0; r0 < g.M; r0 += pn.mr) {
         const int64_t mr = std::min(pn.mr, g.M - r0);
-        if ((e = eval((const char*)g.A + r0 * row_bytes, mr, l.t.VA, pA, l.psA)) != hipSuccess)
+        if (!cuts && (e = eval((const char*)g.A + r0 * row_bytes, mr, l.t.VA, pA, l.psA)) != hipSuccess)
             return e;
         for (int64_t c0 = 0; c0 < g.N; c0 += pn.nc) {
             const int64_t nc = std::min(pn.nc, g.N - c0);
-            if (r0 == 0 || pn.nc < g.N)
-                if ((e = eval((const char*)g.B + c0 * row_bytes, nc, l.t.VB, pB, l.psB)) != hipSuccess)
+            const bool newB = r0 == 0 || pn.nc < g.N;
+            if (cuts) {
+                if ((c0 == 0 || newB) &&
+                    (e = cut(r0, mr, c0, nc, c0 == 0 ? pA : nullptr, newB ? pB : nullptr)) != hipSuccess)
                     return e;
+            } else if (newB && (e = eval((const char*)g.B + c0 * row_bytes, nc, l.t.VB, pB, l.psB)) != hipSuccess) {
+                return e;
+            }
             ResGemmArgs ga;
             ga.A = pA;
             ga.B = pB;
