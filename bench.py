@@ -10,10 +10,13 @@ balanced 8-bit digits (int8bal); the INT8 form with 7-bit sign-magnitude
 digits and the FP64-slice form run beside it with their slice-count rules
 and the same 2^-200 target.  Prints one JSON line.
 
-roofline: the dominant kernel is the slice contraction of the headline form;
-its algorithmic work per launch is 2 M N K S(S+1)/2 int8 operations (S(S+1)/2
-slice multiply-adds per m-double multiply-add), timed with HIP events on the
-call's stream around that kernel.
+roofline: the contraction of the headline form, timed with HIP events on the
+call's stream around all of its kernels.  Where the library contracts the
+digits' residues (md_gemm_planes > 0: this workload in every form) the work
+counted is the INT8 products it runs, 2 M N K times that many planes, and the
+residues' evaluation, interpolation and rounding are inside the time; where it
+multiplies the slices themselves, 2 M N K S(S+1)/2.  Every fraction in the
+output counts work done, of the matrix unit that does it.
 
 The CPU leg, after all GPU work (skip with --no-cpu), is the only user of
 the oracle: cpu_baseline times the exact C oracle on this host's cores over
@@ -55,17 +58,17 @@ PEAK_INT8_TOPS = 5000.0      # MI355X dense INT8 matrix peak, TOP/s
 PEAK_FP64_TFLOPS = 78.6      # MI355X FP64 matrix peak, TFLOP/s
 
 
-TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "k_tri2d_i8_qd4096_traffic.md")
-KERNEL_SOURCES = ("csrc/tri.h", "csrc/trid.h", "csrc/trid.hip", "csrc/slice_common.h", "csrc/renorm.h",
-                  "csrc/tri8_s23_28.hip", "build.py")
+TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "k_res_gemm_qd4096_traffic.md")
+KERNEL_SOURCES = ("csrc/resid.h", "csrc/resid.hip", "csrc/slice_common.h", "csrc/renorm.h", "build.py")
 
 
 def kernel_fingerprint():
-    """sha256 over the sources of the whole-triangle INT8 kernels, first 16
-    hex digits: their headers and unit, the build flags, and of the shared
-    internal header only what they take from it (its integer tiling
-    constants and the kernel argument block), so that unrelated
-    declarations added there keep the stored counter readings valid."""
+    """sha256 over the sources of the residue contraction, first 16 hex
+    digits: its header and unit, the headers it folds and rounds with, the
+    build flags, and of the shared internal header only what it takes from
+    it (its integer tiling constants and the kernel argument block), so that
+    unrelated declarations added there keep the stored counter readings
+    valid."""
     import hashlib
     pkg = os.path.join(ROOT, "paper_2606_20863_amd")
     blob = b"".join(open(os.path.join(pkg, f), "rb").read() for f in KERNEL_SOURCES)
@@ -82,14 +85,28 @@ def kernel_fingerprint():
     return hashlib.sha256(blob).hexdigest()[:16]
 
 
-def int8_kernel_name(info, K):
-    """The INT8 slice contraction kernel the library dispatches for these
-    parameters (digit width beta = 7 or 8): the whole triangle (S <= 32)
+def contraction_work(md, form, info, M, N, K):
+    """(operations of a call's contraction, INT8 planes or None, peak of the
+    unit that runs them in TOP/s): the residue planes where the library takes
+    them, else the S (S + 1) / 2 slice products in the form's own type."""
+    planes = md.lib().md_gemm_planes(md._FORMS[form], M, N, K, info["S"], info["beta"])
+    if planes:
+        return 2.0 * M * N * K * planes, planes, PEAK_INT8_TOPS
+    ops = 2.0 * M * N * K * info["S"] * (info["S"] + 1) / 2
+    return ops, None, PEAK_FP64_TFLOPS if form == "fp64" else PEAK_INT8_TOPS
+
+
+def int8_kernel_name(info, K, planes=None):
+    """The INT8 contraction kernel the library dispatches for these
+    parameters (digit width beta = 7 or 8): the residue planes' product where
+    they are taken; else the whole triangle (S <= 32)
     with two row blocks per wave when the depth is one exactness chunk (for
     balanced S = 27 the variant that shares A through LDS), else one row
     block; two bands over the whole depth for S = 36..64; bands of two row
     blocks per wave otherwise."""
     S, band, b = info["S"], info["band"], info["beta"]
+    if planes:
+        return f"k_res_gemm<{'true' if K > 2048 else 'false'}>"
     if band == S and S <= 32:
         if info["kc"] < K:
             return f"k_tri_i8<{S}, false, {b}>"
@@ -101,7 +118,7 @@ def int8_kernel_name(info, K):
 
 
 def measured_traffic(kernel: str):
-    """HBM bytes per launch of the INT8 slice contraction from the committed
+    """HBM bytes per launch of the residue planes' product from the committed
     counter summary (FETCH_SIZE and WRITE_SIZE, each scaled by its reading
     for a plain 1 GiB copy); None when the summary is missing, covers another
     kernel, or the kernel source changed since the counters were taken."""
@@ -312,8 +329,8 @@ def other_configs(md, torch, steps=3, only=None):
     three products per step); hexa-double 1024^3 forward (leading words
     2^U(-6,6), seed 16).  Per form: milliseconds per step, effective GFLOP/s
     (2 M N K per product), the slice contractions with their folds from HIP
-    events, their fraction of the matrix-core peak (algorithmic work
-    2 M N K S(S+1)/2 per product), and the largest error of 64 sampled
+    events, their fraction of the matrix-core peak (of the unit that runs
+    the contraction: contraction_work), and the largest error of 64 sampled
     entries against the exact product (checked by the CPU leg), of the
     forward product and, with the adjoint, of both gradients."""
     import numpy as np
@@ -381,13 +398,21 @@ def other_configs(md, torch, steps=3, only=None):
             for a, b in evs:
                 hip.hipEventDestroy(ctypes.c_void_p(a))
                 hip.hipEventDestroy(ctypes.c_void_p(b))
-            ops = sum(2.0 * M * N * K * i["S"] * (i["S"] + 1) / 2 for i in infos[:len(calls)])
-            peak = PEAK_FP64_TFLOPS if form == "fp64" else PEAK_INT8_TOPS
+            work = []
+            for c, i in zip(calls, infos):
+                Kc = c["A"].shape[1 if c.get("transA") else 2]
+                Mc = c["A"].shape[2 if c.get("transA") else 1]
+                Nc = c["B"].shape[1 if c.get("transB") else 2]
+                work.append(contraction_work(md, form, i, Mc, Nc, Kc))
+            # the share of the peak that the calls' work needs of their time,
+            # each call's against the unit that runs it
+            ideal = sum(o / (p * 1e12) for o, _, p in work)
             row[form] = {"S": [i["S"] for i in infos[:len(calls)]], "beta": infos[0]["beta"],
                          "steps": nst, "ms_per_step": round(ms, 4),
                          "effective_gflops": round(flop / (ms * 1e-3) / 1e9, 2),
                          "contraction_fold_ms": round(kern, 4),
-                         "frac_peak": round(ops / (kern * 1e-3) / 1e12 / peak, 4)}
+                         "int8_planes": [pl for _, pl, _ in work],
+                         "frac_peak": round(ideal / (kern * 1e-3), 4)}
             defer_error(row[form], "max_log2_err_sampled", Ah, Bh, C)
             if adjoint:
                 # the gradients: dA = W B^T and dB = A^T W on 8 x 8 grids each
@@ -617,7 +642,7 @@ def main():
     if "fp64" not in forms:
         out = {"metric": f"QD-GEMM 4096^3 effective GFLOP/s ({head} form only)",
                "ms_per_call": round(ms8, 4), "gemm_kernel_ms": round(kern8, 4), "S": info8["S"],
-               "kernel": int8_kernel_name(info8, K)}
+               "kernel": int8_kernel_name(info8, K, contraction_work(md, head, info8, M, N, K)[1])}
         if args.configs:
             # profiling runs of chosen workloads beside the one headline form
             del A, B, C8
@@ -652,27 +677,27 @@ def main():
     eff8 = flop / (ms8 * 1e-3) / 1e9
     eff64 = flop / (ms64 * 1e-3) / 1e9
     S8, S64 = info8["S"], info64["S"]
-    ops8 = flop * S8 * (S8 + 1) / 2
-    ops64 = flop * S64 * (S64 + 1) / 2
+    ops8, planes8, _ = contraction_work(md, head, info8, M, N, K)
+    ops64, planes64, peak64 = contraction_work(md, "fp64", info64, M, N, K)
     ach8 = ops8 / (kern8 * 1e-3) / 1e12
     ach64 = ops64 / (kern64 * 1e-3) / 1e12
 
-    kname8 = int8_kernel_name(info8, K)
+    kname8 = int8_kernel_name(info8, K, planes8)
     traffic8 = measured_traffic(kname8)
     traffic8 = None if traffic8 is None else int(traffic8)
 
-    def int8_summary(info, ms, kern, steps):
+    def int8_summary(form, info, ms, kern, steps):
         S = info["S"]
-        ops = flop * S * (S + 1) / 2
+        ops, planes, _ = contraction_work(md, form, info, M, N, K)
         return {"S": S, "beta": info["beta"], "kc": info["kc"], "band": info["band"],
                 "steps": steps, "ms_per_call": round(ms, 4), "gemm_kernel_ms": round(kern, 4),
-                "kernel": int8_kernel_name(info, K),
+                "kernel": int8_kernel_name(info, K, planes), "int8_planes": planes,
                 "effective_gflops": round(flop / (ms * 1e-3) / 1e9, 3),
                 "mfma_int8_tops": round(ops / (kern * 1e-3) / 1e12, 3),
                 "max_log2_err_sampled": None,
                 "certified_log2_bound": round(info["log2_bound"], 2)}
 
-    head_form = int8_summary(info8, ms8, kern8, args.steps)
+    head_form = int8_summary(head, info8, ms8, kern8, args.steps)
     head_form["digits"] = ("balanced 8-bit digits in [-128, 127] on the grid 2^(E+2)" if head == "int8bal"
                            else "7-bit sign-magnitude digits")
     out = {
@@ -697,12 +722,13 @@ def main():
         "fp64_form": {"S": S64, "beta": info64["beta"], "kc": info64["kc"], "band": info64["band"],
                       "steps": args.fp64_steps, "ms_per_call": round(ms64, 4),
                       "gemm_kernel_ms": round(kern64, 4), "effective_gflops": round(eff64, 3),
-                      "mfma_tflops": round(ach64, 3), "frac_fp64_peak": round(ach64 / PEAK_FP64_TFLOPS, 4),
+                      "int8_planes": planes64, "mfma_tops": round(ach64, 3),
+                      "frac_peak": round(ach64 / peak64, 4),
                       "max_log2_err_sampled": None,
                       "certified_log2_bound": round(info64["log2_bound"], 2)},
         "int8_over_fp64": round(eff8 / eff64, 3),
         "int8_sign_magnitude_form": None if sm is None else dict(
-            int8_summary(sm[1], sm[2], sm[3], args.sm_steps),
+            int8_summary("int8", sm[1], sm[2], sm[3], args.sm_steps),
             digits="7-bit sign-magnitude digits (the paper's bit-field cut)",
             headline_speedup=round(sm[2] / ms8, 3)),
         "ordinary_form": None if ord_ms is None else {
@@ -714,8 +740,13 @@ def main():
         "roofline": {"bound": "mfma", "kernel": kname8,
                      "achieved": round(ach8, 3), "peak": PEAK_INT8_TOPS, "unit": "TFLOP/s",
                      "frac": round(ach8 / PEAK_INT8_TOPS, 4), "traffic": traffic8,
-                     "work_per_launch": f"2*M*N*K*S(S+1)/2 = {ops8:.4e} int8 ops (unit: int8 TOP/s)",
-                     "algorithmic_bytes_per_launch": int(2 * S8 * M * K + 8 * m * M * N)},
+                     "work_per_launch": (f"2*M*N*K*{planes8} residue planes" if planes8 else "2*M*N*K*S(S+1)/2")
+                     + f" = {ops8:.4e} int8 ops (unit: int8 TOP/s; the time includes the digits' residues, "
+                       "the interpolation and the rounding)",
+                     # the planes' product alone: both operands' residues read, one residue per output
+                     # and plane written (the last diagonal's sums are written as 32-bit words)
+                     "algorithmic_bytes_per_launch": int(planes8 * K * (M + N) + planes8 * M * N if planes8
+                                                         else 2 * S8 * M * K + 8 * m * M * N)},
     }
     if not args.no_split:
         out["depth_split"] = depth_split(md, torch, A, B, C8, info8)

@@ -157,7 +157,10 @@ typedef struct md_opts {
     md_debug *dbg;         /* optional debug dump */
     md_info *info;         /* optional: receives the chosen parameters */
     void *ev_gemm_begin;   /* optional hipEvent_t pair (caller-owned), recorded on */
-    void *ev_gemm_end;     /*   `stream` right before / after the slice contraction */
+    void *ev_gemm_end;     /*   `stream` right before / after the slice contraction
+                            *   (where md_gemm_planes is not 0, the digits' residues,
+                            *   interpolation and rounding included, and with m <= 4
+                            *   and few digits the split) */
     int validate;          /* nonzero: check the input preconditions first (one read of
                               the inputs and one synchronisation); MD_EINPUT, with C
                               untouched and md_info.input_flags set, if any fails */

@@ -624,8 +624,12 @@ struct ResLoads {
 // loads left out it runs at 92% of the matrix cores' peak on zeros, with
 // them at 72% (a load instruction issued among matrix instructions holds the
 // wave less than eight in a row: 3.55 against 3.30 POP/s on zeros), and on
-// residues the clock falls with the power drawn.  v_mfma_i32_32x32x32_i8 on
-// the same tile was 10% slower on residues.
+// residues the clock falls with the power drawn (4096^3, 164 planes: 64% of
+// the cycles at 1.75 GHz, 9.3 to 9.8 ms, 2.3 to 2.4 POP/s).
+// v_mfma_i32_32x32x32_i8 on the same tile was 10% slower on residues.  No
+// change from every tile reading one panel, a fifth LDS slot, B straight to
+// registers, the row blocks of a depth step side by side in memory, or
+// stores past the caches.
 // WIDE: sums that one rounding of the quotient in single precision could
 // leave outside a byte (see launch_resid).
 template <bool WIDE>
