@@ -1160,26 +1160,26 @@ bool res_plan(bool balanced, bool fp64, int S, int beta, int64_t K, ResPlan& r)
 
 // Expected microseconds of the residue contraction and of the slice products
 // for one product, and the line between them.  Fitted to both paths' times
-// on one MI355X over m = 1 .. 16, the three forms, cubes from 64 to 3072,
-// 4096 x 256 x 1024, 256 x 256 x 4096, 2048 x 2048 x 256, 1024 x 1024 x 4096
-// and 4096 x 64 x 4096 (within about 15% from 100 us up).
+// on one MI355X over m = 1 .. 16, the three forms, cubes from 64 to 3072 and
+// up to nine oblong sizes from 64 x 64 x 4096 to 1024 x 1024 x 128 (the
+// residues within 11%, 16% once).
 //
 // Residues: 256 x 256 tiles of all planes in rounds of one per compute unit,
-// 0.85 us per 64 depths and 7 us of reduction each (0.9 and 3 from 33 digits
-// on); cutting and evaluating up to 32 digits 5.3e6 bytes of words and
-// residues per us, evaluating more 3.4e6 residues per us; the interpolation
-// by its matrix products and the rounding; fixed costs that grow with the
-// planes (the evaluation's loop over them is serial).  Up to 32 digits it is
-// within 10% of the times measured over m = 1, 2 and 4, cubes from 64 to
-// 3072 and nine oblong sizes.  Slice products: the INT8 kernels' 64 x 32 tiles in rounds,
+// 0.85 us per 64 depths and 5 to 7 us of reduction each; cutting and
+// evaluating up to 32 digits 5.3e6 bytes of words and residues per us,
+// evaluating more 4.5e6 residues per us; the interpolation and the rounding;
+// fixed costs that grow with the planes (the evaluation's loop over them is
+// serial).  Slice products: the INT8 kernels' 64 x 32 tiles in rounds,
 // S (S+1) matrix instructions per 64 depths; the FP64 kernel at 62 TFLOP/s,
 // or a tile's serial depth where tiles are few.
 //
-// So FP64 digits change over below 384^3 doubles and double-doubles (57 us
-// against 47 and 93 against 65) and below 128^3 quad-doubles (115 against
-// 90); INT8 octo-doubles at about 256^3 (181 against 168), hexa-doubles at
-// 128^3, quad-doubles at about 1536^3 (27 balanced digits: 952 against 921;
-// 1024^3: 295 against 396; 3072^3: 6624 against 5588), double-doubles never.
+// So (slices against residues, us) FP64 digits change over below 384^3
+// doubles and double-doubles (57 against 47 and 93 against 65) and below
+// 128^3 quad-doubles (115 against 90); INT8 octo-doubles at about 256^3 (52
+// balanced digits: 143 against 133; 192^3: 115 against 127), hexa-doubles
+// below 96^3 (368 against 240), quad-doubles between 1536^3 (27 balanced
+// digits: 952 against 921) and 2048^3 (1989 against 1825), double-doubles
+// never.
 bool res_pays(const ResPlan& r, int64_t M, int64_t N, int64_t K, bool duo, double tri_us)
 {
     const double dM = (double)M, dN = (double)N, dK = (double)K, dS = r.S;
@@ -1191,18 +1191,18 @@ bool res_pays(const ResPlan& r, int64_t M, int64_t N, int64_t K, bool duo, doubl
         r.SB <= 32 ? 25 + 0.07 * planes + rounds * (steps * 0.85 + 6.7) +
                          (dM + dN) * steps * 64 * (planes + 8 * words) / 5.3e6 +
                          dM * dN * 1e-6 * (21 + 0.45 * words * res_limbs(r, K))
-                   : 60 + 0.25 * r.N + 0.18 * planes + rounds * (steps * 0.9 + 3) +
-                         (dM + dN) * steps * 64 * planes / 3.4e6 +
-                         dM * dN * 1e-6 *
-                             (12 + 4.0 * r.P * ((r.L + 15) / 16) * ((r.N + 31) / 32) + 0.6 * words * res_limbs(r, K));
+                   : 13 + 0.265 * planes + rounds * (steps * 0.864 + 4.7) +
+                         (dM + dN) * steps * 64 * planes / 4.5e6 +
+                         dM * dN * 1e-6 * (19 + 0.9 * words * res_limbs(r, K));
     double slices;
     if (r.nb) {
         slices = std::min(40.0, 18 + 2.4 * dS) + std::max(dM * dN * dK * dS * (dS + 1) / 62e6, 0.0045 * dK * dS * (dS + 1));
     } else if (tri_us > 0) {
         slices = 8 + 1.03 * tri_us;
     } else {
-        const double per = duo && r.S <= kDuoMax ? 0.0113 : 0.0134;
-        slices = 30 + std::ceil(std::ceil(dM / 64) * std::ceil(dN / 32) / 256) *
+        const bool two = duo && r.S <= kDuoMax;
+        const double per = two ? 0.0095 : 0.0134;
+        slices = (two ? 25 : 30) + std::ceil(std::ceil(dM / 64) * std::ceil(dN / 32) / 256) *
                           (std::ceil(dK / 64) * dS * (dS + 1) * per + 15);
     }
     return residues * 1.03 < slices;
