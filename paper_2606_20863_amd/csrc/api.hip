@@ -342,7 +342,7 @@ int fixed_limbs_of(int beta, int S, int64_t K)
 // depths plus 15 us of prologue and fold; the parts' limbs at 4 TB/s, and 6
 // us for the second launch.  (4096 x 24 x 4096 quad-doubles, 64 tiles: 442
 // us whole.)  A depth over several exactness chunks had one row block per
-// wave and a fold after each chunk, about 1.3 times the time per depth.
+// wave and a fold after each chunk, about 1.3 times the time per depth.  S >= 1.
 struct TriParts {
     int parts = 1, nlimb = 0;
     int64_t per = 0;       // depth chunks of a part
@@ -383,7 +383,7 @@ bool take_residues(int form, int S, int beta, int64_t M, int64_t N, int64_t K, b
 {
     // products too small for either path's arithmetic to matter (64^3
     // double-doubles, say): without the estimate
-    if ((double)M * N * K * S * S < 1.5e8)
+    if (S < 1 || (double)M * N * K * S * S < 1.5e8)
         return false;
     const double tri = is_i8(form) && S <= kTriMaxI8 ? tri_parts(form, beta, S, M, N, K).us : 0.0;
     return res_plan(form == MD_FORM_INT8_BAL, form == MD_FORM_FP64, S, beta, K, rp) &&
@@ -641,7 +641,7 @@ size_t md_gemm_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S)
     if (global)
         bytes += (size_t)gd_elements(M, N, S, is_i8(form) ? 2 : 1) * sizeof(int64_t) + 256;
     // the depth parts' integers
-    if (is_i8(form) && S <= kTriMaxI8 && K > 0) {
+    if (is_i8(form) && S >= 1 && S <= kTriMaxI8 && K > 0) {
         const TriParts tp = tri_parts(form, form == MD_FORM_INT8 ? 7 : 8, S, M, N, K);
         if (tp.parts > 1)
             bytes += tp.bytes + 256;
