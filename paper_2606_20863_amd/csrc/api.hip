@@ -250,11 +250,23 @@ struct Scratch {
     char* user = nullptr;
     size_t user_bytes = 0, used = 0;
     hipStream_t st = nullptr;
-    void* owned[8] = {};
+    static constexpr int kOwned = 12;   // pool blocks of one call (at most nine are asked for)
+    void* owned[kOwned] = {};
     int nowned = 0;
 
-    // whether the caller's workspace still holds this much (the pool: always)
-    bool holds(size_t bytes) const { return !user || used + (bytes + 255) / 256 * 256 <= user_bytes; }
+    // What is held now, and back to it: an optional path that does not get
+    // all of its scratch leaves none of it to the path taken instead.
+    struct Mark {
+        size_t used;
+        int nowned;
+    };
+    Mark mark() const { return {used, nowned}; }
+    void rewind(Mark m)
+    {
+        used = m.used;
+        while (nowned > m.nowned)
+            (void)hipFreeAsync(owned[--nowned], st);
+    }
 
     int get(size_t bytes, void** out)
     {
@@ -275,18 +287,14 @@ struct Scratch {
             (void)hipGetLastError();
             return MD_ENOMEM;
         }
-        if (nowned == 8) {
+        if (nowned == kOwned) {
             (void)hipFreeAsync(*out, st);
             return MD_ENOMEM;
         }
         owned[nowned++] = *out;
         return MD_OK;
     }
-    ~Scratch()
-    {
-        for (int i = 0; i < nowned; ++i)
-            (void)hipFreeAsync(owned[i], st);
-    }
+    ~Scratch() { rewind({0, 0}); }
 };
 
 // Validation mode: the OR of the precondition flags of both operands, on
@@ -871,8 +879,8 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
             const bool cuts = res_cuts(rp, m);   // the evaluation cuts the digits itself: no digit planes
             const size_t bA = cuts ? 0 : digits_bytes(MD_FORM_INT8, M, K, rp.SB);
             const size_t bB = cuts ? 0 : digits_bytes(MD_FORM_INT8, N, K, rp.SB);
-            if (scr.holds(bA + bB + pn.bytes + 512) && (cuts || (!scr.get(bA, &dA) && !scr.get(bB, &dB))) &&
-                !scr.get(pn.bytes, &work)) {
+            const Scratch::Mark before = scr.mark();
+            if (!scr.get(pn.bytes, &work) && (cuts || (!scr.get(bA, &dA) && !scr.get(bB, &dB)))) {
                 GemmArgs ga;
                 memset(&ga, 0, sizeof(ga));
                 ga.A = dA;
@@ -912,6 +920,7 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
                     fill_info(o.info, ch, T, o.validate != 0);
                 return MD_OK;
             }
+            scr.rewind(before);
         }
     }
 
@@ -938,17 +947,6 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
         }
     }
 
-    // depth parts of the whole triangle, where the scratch holds their integers
-    TriParts tp;
-    int32_t* partX = nullptr;
-    if (!fx && !dbg && is_i8(o.form) && band == S && S <= kTriMaxI8) {
-        tp = tri_parts(o.form, beta, S, M, N, K);
-        void* p = nullptr;
-        const size_t dig = digits_bytes(o.form, M, K, S) + digits_bytes(o.form, N, K, S);
-        if (tp.parts > 1 && scr.holds(dig + tp.bytes + 256) && !scr.get(tp.bytes, &p))
-            partX = (int32_t*)p;
-    }
-
     void *dA, *dB;
     int rc = scr.get(digits_bytes(o.form, M, K, S), &dA);
     if (rc)
@@ -956,6 +954,17 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
     rc = scr.get(digits_bytes(o.form, N, K, S), &dB);
     if (rc)
         return rc;
+
+    // depth parts of the whole triangle, where the scratch holds their
+    // integers beside the digits
+    TriParts tp;
+    int32_t* partX = nullptr;
+    if (!fx && !dbg && is_i8(o.form) && band == S && S <= kTriMaxI8) {
+        tp = tri_parts(o.form, beta, S, M, N, K);
+        void* p = nullptr;
+        if (tp.parts > 1 && !scr.get(tp.bytes, &p))
+            partX = (int32_t*)p;
+    }
 
     {
         const SplitSide pa{opA, E, Mp / kRowBlock, dA, dbg ? dbg->digits_A : nullptr};
