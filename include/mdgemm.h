@@ -201,7 +201,7 @@ int md_gemm(int m, int64_t M, int64_t N, int64_t K, const double *A, const doubl
  *   opts may be NULL (FP64 form, MD_S_RHO rule, T = 50 m).
  * Graph capture: with opts->force_S (or opts->s_hint and opts->cert) set,
  * opts->validate and opts->dbg clear and a workspace of at least
- * md_gemm_workspace_size bytes, the call only launches kernels on `stream`
+ * md_gemm_workspace_least bytes, the call only launches kernels on `stream`
  * (no allocation, copy, memset or synchronisation), so it can be captured
  * into a HIP graph and replayed.
  * Replays reuse the workspace: replays (or calls) that share one must not
@@ -220,9 +220,11 @@ int md_gemm_ex(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, c
  * global memory (held until the process ends), so the call makes no
  * allocation or free of any kind.
  *   opts->workspace must be NULL (MD_EINVAL_OPT otherwise).
- *   A call whose scratch (md_gemm_workspace_size for its form and S) would
- *   exceed the array returns MD_ENOMEM with C untouched; with the slice
- *   rule this is known only after the exponent step has run on the stream.
+ *   A call whose md_gemm_workspace_size for its form and S exceeds the array
+ *   runs the slice products where their scratch fits; one whose
+ *   md_gemm_workspace_least exceeds it returns MD_ENOMEM with C untouched;
+ *   with the slice rule this is known only after the exponent step has run
+ *   on the stream.
  * The array keeps the last call's contents; no step reads scratch it has
  * not written in the same call.  All calls on one device share the array:
  * calls that overlap in time on one device (different streams or host
@@ -388,9 +390,16 @@ int md_fixed_round(int m, int64_t count, int nlimb, const int32_t *X, const int3
  */
 int md_choose_params(int form, int64_t K, int T, int G, int *beta, int *S, int *kc, int *band);
 
-/* Scratch bytes an md_gemm_ex call with these sizes, form and S needs (the
- * workspace that lets a call allocate nothing). */
+/* Scratch bytes with which an md_gemm_ex call of these sizes, form and S
+ * runs its fastest way (the residue planes or the depth parts included; up
+ * to about 9 GiB).  A call with less runs the slice products, with the same
+ * results, as long as it has md_gemm_workspace_least bytes; below that it
+ * returns MD_ENOMEM.  With either size a call allocates nothing. */
 size_t md_gemm_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S);
+
+/* Scratch bytes that such a call needs at least: those of the slice
+ * products, at most md_gemm_workspace_size. */
+size_t md_gemm_workspace_least(int form, int64_t M, int64_t N, int64_t K, int S);
 
 /* INT8 matrix products of depth K by which md_gemm_ex contracts these sizes,
  * S and beta where it takes the residues of the digits (csrc/resid.h; with

@@ -130,6 +130,8 @@ def lib():
     L.md_choose_params.restype = i32
     L.md_gemm_workspace_size.argtypes = [i32, i64, i64, i64, i32]
     L.md_gemm_workspace_size.restype = ctypes.c_size_t
+    L.md_gemm_workspace_least.argtypes = L.md_gemm_workspace_size.argtypes
+    L.md_gemm_workspace_least.restype = ctypes.c_size_t
     L.md_gemm_planes.argtypes = [i32, i64, i64, i64, i32, i32]
     L.md_gemm_planes.restype = i32
     L.md_workspace_size.argtypes = [i32, i64, i64, i64, i32]
@@ -219,21 +221,35 @@ def read_cert(cert: torch.Tensor) -> dict:
 _S_SEEN: dict = {}
 
 
-def _auto_workspace(key, size_of_S, S, device, stream):
+def _auto_workspace(key, sizes_of_S, S, device, stream):
     """Scratch for a call from torch's caching allocator: with it the library
     allocates nothing and a call only queues kernels (its own pool's
     stream-ordered allocation and release put work on the GPU's queue in
     every call, 10-70 us of it measured per call).  Sized for S, else for
     the S this shape and these options took last time; None when neither is
-    known (the library's pool serves that call)."""
+    known (the library's pool serves that call).  ``sizes_of_S`` gives the
+    sizes to ask for in turn, the fastest way's first and the least last:
+    where the device has no room for any, the pool serves the call too, and
+    the library takes from it what it can get."""
     if S <= 0:
         S = _S_SEEN.get(key, 0)
     if S <= 0:
         return None
-    ws = torch.empty(int(size_of_S(S)), dtype=torch.uint8, device=device)
-    if stream is not None:
-        ws.record_stream(stream)
-    return ws
+    for size in sizes_of_S(S):
+        try:
+            ws = torch.empty(int(size), dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            continue
+        if stream is not None:
+            ws.record_stream(stream)
+        return ws
+    return None
+
+
+def _gemm_sizes(form, M, N, K, S):
+    """Scratch sizes of a product, the fastest way's, then the least."""
+    yield lib().md_gemm_workspace_size(form, M, N, K, S)
+    yield lib().md_gemm_workspace_least(form, M, N, K, S)
 
 
 def _run_with_scratch(call, opts: "MDOpts", ws, key, info: "MDInfo"):
@@ -281,8 +297,9 @@ def gemm_ex(A: torch.Tensor, B: torch.Tensor, C: torch.Tensor | None = None, *, 
     C untouched, when an entry breaks them).  ``s_hint`` (with ``cert``, a
     ``new_cert()`` buffer): run on that S without waiting for the rule; the
     device writes the data's certificate into ``cert`` (``read_cert``).
-    ``workspace``: a contiguous device buffer of at least
-    ``md_gemm_workspace_size`` bytes (the call then allocates nothing).
+    ``workspace``: a contiguous device buffer of ``md_gemm_workspace_size``
+    bytes, or of at least ``md_gemm_workspace_least`` (the call then allocates
+    nothing).
     ``noalloc``: call md_gemm_ex_noalloc (the library's own fixed scratch
     array, no workspace; C must then be given to allocate nothing at all).
     Without a workspace the scratch comes from torch's caching allocator
@@ -344,7 +361,7 @@ def gemm_ex(A: torch.Tensor, B: torch.Tensor, C: torch.Tensor | None = None, *, 
 
     if workspace is None and not noalloc and not debug and not pool:
         key = ("gemm", form, rule, target_bits, force_beta, m, M, N, K, bool(transA), bool(transB))
-        ws = _auto_workspace(key, lambda S: lib().md_gemm_workspace_size(_FORMS[form], M, N, K, S),
+        ws = _auto_workspace(key, lambda S: _gemm_sizes(_FORMS[form], M, N, K, S),
                              force_S or s_hint, A.device, stream)
         _run_with_scratch(call, opts, ws, key, info)
     else:
@@ -400,7 +417,7 @@ def dot_ex(X: torch.Tensor, Y: torch.Tensor, out: torch.Tensor | None = None, *,
 
     if workspace is None and not pool:
         key = ("dot", form, rule, target_bits, force_beta, m, batch, n)
-        ws = _auto_workspace(key, lambda S: lib().md_dot_workspace_size(_FORMS[form], batch, n, S),
+        ws = _auto_workspace(key, lambda S: (lib().md_dot_workspace_size(_FORMS[form], batch, n, S),),
                              force_S or s_hint, X.device, stream)
         _run_with_scratch(call, opts, ws, key, info)
     else:

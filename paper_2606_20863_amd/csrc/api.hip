@@ -635,7 +635,8 @@ size_t md_dot_workspace_size(int form, int64_t batch, int64_t n, int S)
            (size_t)batch * 24 + 4096;
 }
 
-size_t md_gemm_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S)
+// The slice products' scratch, without the depth parts.
+size_t md_gemm_workspace_least(int form, int64_t M, int64_t N, int64_t K, int S)
 {
     size_t bytes = small_bytes(M, N) + digits_bytes(MD_FORM_INT8, M, K, 1) +
                    digits_bytes(MD_FORM_INT8, N, K, 1) + digits_bytes(form, M, K, S) +
@@ -648,6 +649,12 @@ size_t md_gemm_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S)
                                     : (size_t)4 * ncol * 256 * sizeof(int64_t) > 160 * 1024;
     if (global)
         bytes += (size_t)gd_elements(M, N, S, is_i8(form) ? 2 : 1) * sizeof(int64_t) + 256;
+    return bytes;
+}
+
+size_t md_gemm_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S)
+{
+    size_t bytes = md_gemm_workspace_least(form, M, N, K, S);
     // the depth parts' integers
     if (is_i8(form) && S >= 1 && S <= kTriMaxI8 && K > 0) {
         const TriParts tp = tri_parts(form, form == MD_FORM_INT8 ? 7 : 8, S, M, N, K);

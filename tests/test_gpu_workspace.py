@@ -1,0 +1,40 @@
+"""Products on workspaces of different sizes (needs an MI355X): the size that
+the fastest way takes, the least one, and one byte less than the fastest way
+takes give the same words, for products that run the residue contraction, the
+depth parts, the bands with their sum buffer and the FP64 slices.
+"""
+import numpy as np
+import pytest
+import torch
+
+import mdinputs
+import paper_2606_20863_amd as md
+
+pytestmark = pytest.mark.gpu
+
+# m, form, M, N, K, whether more than the least is of use
+CASES = [
+    (8, "int8bal", 300, 513, 640, True),      # residues, digit planes apart
+    (2, "fp64", 513, 700, 640, True),         # residues, digits cut on the way
+    (4, "int8", 700, 24, 1500, True),         # depth parts
+    (16, "int8bal", 16, 24, 24, False),       # bands
+    (4, "fp64", 64, 80, 64, False),           # FP64 slices
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"m{c[0]}-{c[1]}-{c[2]}x{c[3]}x{c[4]}")
+def test_same_words_on_every_size(case):
+    m, form, M, N, K, more = case
+    rng = np.random.Generator(np.random.PCG64(M + K))
+    dA = torch.from_numpy(mdinputs.mdouble(rng, m, (M, K), ("uniform",))).cuda()
+    dB = torch.from_numpy(mdinputs.mdouble(rng, m, (K, N), ("uniform",))).cuda()
+    want, info = md.gemm_ex(dA, dB, form=form)
+    S, beta = info["S"], info["beta"]
+    full, least = md._gemm_sizes(md._FORMS[form], M, N, K, S)
+    assert (full > least) == more
+    for size in (full, least, max(least, full - 4097)):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        C, _ = md.gemm_ex(dA, dB, form=form, force_S=S, force_beta=beta, workspace=ws)
+        assert torch.equal(C, want), size
+        C, _ = md.gemm_ex(dA, dB, form=form, workspace=ws)
+        assert torch.equal(C, want), size
