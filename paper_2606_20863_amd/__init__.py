@@ -216,26 +216,26 @@ def read_cert(cert: torch.Tensor) -> dict:
     return MDCert.from_buffer_copy(raw).as_dict()
 
 
-# S of the last call per shape and options (keys below), for sizing the
-# scratch of the next one before the slice rule has run
-_S_SEEN: dict = {}
+# Per shape and options (keys below) the slice counts that the rule chose so
+# far and the scratch sizes that hold each of them, for the next call, whose S
+# is not known before the rule has run.  The largest, not the last: a call on
+# less than its S takes falls back to the slice products (double-doubles
+# 2048^3 in FP64 digits, S = 5 and 6 by turns: every other call 4 times
+# longer).  Until a rule call of the shape, a forced or hinted call's.
+_SIZES: dict = {}
 
 
 def _auto_workspace(key, sizes_of_S, S, device, stream):
     """Scratch for a call from torch's caching allocator: with it the library
     allocates nothing and a call only queues kernels (its own pool's
     stream-ordered allocation and release put work on the GPU's queue in
-    every call, 10-70 us of it measured per call).  Sized for S, else for
-    the S this shape and these options took last time; None when neither is
-    known (the library's pool serves that call).  ``sizes_of_S`` gives the
-    sizes to ask for in turn, the fastest way's first and the least last:
-    where the device has no room for any, the pool serves the call too, and
-    the library takes from it what it can get."""
-    if S <= 0:
-        S = _S_SEEN.get(key, 0)
-    if S <= 0:
-        return None
-    for size in sizes_of_S(S):
+    every call, 10-70 us of it measured per call).  Sized for S, else as
+    ``_SIZES`` says; None when neither is known (the library's pool serves
+    that call).  ``sizes_of_S`` gives the sizes to ask for in turn, the
+    fastest way's first and the least last: where the device has no room for
+    any, the pool serves the call too, and the library takes from it what it
+    can get."""
+    for size in sizes_of_S(S) if S > 0 else _SIZES.get(key, ((), ()))[1]:
         try:
             ws = torch.empty(int(size), dtype=torch.uint8, device=device)
         except torch.OutOfMemoryError:
@@ -252,7 +252,18 @@ def _gemm_sizes(form, M, N, K, S):
     yield lib().md_gemm_workspace_least(form, M, N, K, S)
 
 
-def _run_with_scratch(call, opts: "MDOpts", ws, key, info: "MDInfo"):
+def _note_sizes(key, S, ruled, sizes_of_S):
+    """Records the slice count a call of ``key`` took."""
+    seen, sizes = _SIZES.get(key, ((), ()))
+    if S <= 0 or S in seen or (sizes and not ruled):
+        return
+    if len(_SIZES) >= 4096 and key not in _SIZES:
+        _SIZES.clear()   # bounded: a process that meets many shapes starts over
+    new = tuple(sizes_of_S(S))
+    _SIZES[key] = (seen + (S,) if ruled else (), tuple(map(max, sizes, new)) if seen else new)
+
+
+def _run_with_scratch(call, opts: "MDOpts", ws, key, sizes_of_S, info: "MDInfo"):
     """call() with ws as the workspace; a call whose slice rule chose a larger
     S than ws holds stops with MD_ENOMEM before it writes any output, and
     runs again on the library's pool.  Records the S taken under key."""
@@ -263,10 +274,7 @@ def _run_with_scratch(call, opts: "MDOpts", ws, key, info: "MDInfo"):
         opts.workspace, opts.workspace_bytes = None, 0
         rc = call()
     _check(rc, info)
-    if key is not None:
-        if len(_S_SEEN) >= 4096 and key not in _S_SEEN:
-            _S_SEEN.clear()   # bounded: a process that meets many shapes starts over
-        _S_SEEN[key] = info.S
+    _note_sizes(key, info.S, opts.force_S <= 0 and opts.s_hint <= 0, sizes_of_S)
     return rc
 
 
@@ -361,9 +369,12 @@ def gemm_ex(A: torch.Tensor, B: torch.Tensor, C: torch.Tensor | None = None, *, 
 
     if workspace is None and not noalloc and not debug and not pool:
         key = ("gemm", form, rule, target_bits, force_beta, m, M, N, K, bool(transA), bool(transB))
-        ws = _auto_workspace(key, lambda S: _gemm_sizes(_FORMS[form], M, N, K, S),
-                             force_S or s_hint, A.device, stream)
-        _run_with_scratch(call, opts, ws, key, info)
+
+        def sizes(S):
+            return _gemm_sizes(_FORMS[form], M, N, K, S)
+
+        ws = _auto_workspace(key, sizes, force_S or s_hint, A.device, stream)
+        _run_with_scratch(call, opts, ws, key, sizes, info)
     else:
         _check(call(), info)
     return C, info.as_dict()
@@ -417,9 +428,12 @@ def dot_ex(X: torch.Tensor, Y: torch.Tensor, out: torch.Tensor | None = None, *,
 
     if workspace is None and not pool:
         key = ("dot", form, rule, target_bits, force_beta, m, batch, n)
-        ws = _auto_workspace(key, lambda S: (lib().md_dot_workspace_size(_FORMS[form], batch, n, S),),
-                             force_S or s_hint, X.device, stream)
-        _run_with_scratch(call, opts, ws, key, info)
+
+        def sizes(S):
+            return (lib().md_dot_workspace_size(_FORMS[form], batch, n, S),)
+
+        ws = _auto_workspace(key, sizes, force_S or s_hint, X.device, stream)
+        _run_with_scratch(call, opts, ws, key, sizes, info)
     else:
         _check(call(), info)
     return out, info.as_dict()

@@ -38,3 +38,21 @@ def test_same_words_on_every_size(case):
         assert torch.equal(C, want), size
         C, _ = md.gemm_ex(dA, dB, form=form, workspace=ws)
         assert torch.equal(C, want), size
+
+
+def test_slice_count_changes_from_call_to_call():
+    """One shape through gemm with data of two spans by turns: the words of
+    the pool's calls every time."""
+    m, M, N, K = 2, 640, 520, 700
+    rng = np.random.Generator(np.random.PCG64(11))
+    A = torch.from_numpy(mdinputs.mdouble(rng, m, (M, K), ("uniform",))).cuda()
+    B = torch.from_numpy(mdinputs.mdouble(rng, m, (K, N), ("uniform",))).cuda()
+    small, even = A.clone(), B.clone()
+    small[:, :, ::2] *= 2.0 ** -24         # every other depth far below the rows' exponents,
+    even[:, 1::2] = 0.0                    # and the columns meet those depths alone
+    cases = [(A, B), (small, even)]
+    want = [md.gemm_ex(a, b, pool=True) for a, b in cases]
+    assert len({i["S"] for _, i in want}) > 1
+    for _ in range(3):
+        for (a, b), (C, _) in zip(cases, want):
+            assert torch.equal(md.gemm(a, b), C)

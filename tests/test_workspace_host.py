@@ -66,3 +66,43 @@ def test_less_scratch_where_memory_is_short(memory):
 def test_least_is_not_above_the_size(form, M, N, K, S):
     full, least = md._gemm_sizes(form, M, N, K, S)
     assert 0 < least <= full
+
+
+def test_scratch_of_the_largest_slice_count(memory, monkeypatch):
+    """A shape whose slice count changes from call to call: the scratch holds
+    the planes of every count met so far."""
+    n = 2048
+    monkeypatch.setattr(md, "_SIZES", {})
+
+    def sizes(S):
+        return md._gemm_sizes(0, n, n, n, S)
+
+    def call(S, force=0):
+        """One call whose rule takes S; what it asked torch for."""
+        opts, info = md.MDOpts(), md.MDInfo()
+        opts.force_S = force
+        memory.asked = []
+        ws = md._auto_workspace("shape", sizes, force, "cpu", None)
+        info.S = S
+        md._run_with_scratch(lambda: 0, opts, ws, "shape", sizes, info)
+        return memory.asked
+
+    five, six = next(sizes(5)), next(sizes(6))
+    assert five < six
+    assert call(5) == []                       # nothing known: the pool
+    assert call(6) == [five]
+    assert call(5) == [six] and call(6) == [six] and call(5) == [six]
+    # a forced count has its own size and leaves the rule's as it is
+    assert call(8, force=8) == [next(sizes(8))] and call(5) == [six]
+    # until the rule has run, a forced count's serves
+    md._SIZES.clear()
+    call(8, force=8)
+    assert call(5) == [next(sizes(8))] and call(5) == [five]
+    assert call(0) == [five] and call(5) == [five]   # depth 0: no slices
+
+
+def test_sizes_are_bounded(memory, monkeypatch):
+    monkeypatch.setattr(md, "_SIZES", {})
+    for k in range(5000):
+        md._note_sizes(k, 5, True, lambda S: (S, S))
+    assert len(md._SIZES) <= 4096 and 4999 in md._SIZES
