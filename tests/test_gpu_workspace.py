@@ -56,3 +56,21 @@ def test_slice_count_changes_from_call_to_call():
     for _ in range(3):
         for (a, b), (C, _) in zip(cases, want):
             assert torch.equal(md.gemm(a, b), C)
+
+
+def test_pool_gives_large_scratch_back():
+    """A product on the library's pool whose planes take more than 4 GiB:
+    with the call ended, no more than that stays taken from the device."""
+    m, n, S = 4, 4096, 27
+    assert next(md._gemm_sizes(2, n, n, n, S)) > 6 << 30
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    A = torch.rand((m, n, n), generator=gen, dtype=torch.float64, device="cuda") - 0.5
+    A *= 2.0 ** (-54 * torch.arange(m, device="cuda", dtype=torch.float64))[:, None, None]
+    C = torch.empty_like(A)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    before = torch.cuda.mem_get_info()[0]
+    md.gemm_ex(A, A.clone(), C, form="int8bal", force_S=S, force_beta=8, pool=True)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    assert before - torch.cuda.mem_get_info()[0] <= (4 << 30) + (64 << 20)
