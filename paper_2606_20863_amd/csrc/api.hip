@@ -407,6 +407,16 @@ bool take_residues(int form, int S, int beta, int64_t M, int64_t N, int64_t K, b
            res_pays(rp, M, N, K, duo, tri) && res_panels(rp, M, N, K, pn);
 }
 
+// Digit planes of both operands that a panel of residue planes needs beside
+// it, where the evaluation does not cut the digits itself: none where they fit
+// the place of the products' residues, which are written after the last digit
+// has been read (several panels read them again).
+size_t res_digits(const ResPlan& rp, const ResPanels& pn, int64_t M, int64_t N, int64_t K)
+{
+    const size_t b = digits_bytes(MD_FORM_INT8, M, K, rp.SB) + digits_bytes(MD_FORM_INT8, N, K, rp.SB);
+    return pn.single && pn.res_at + b <= pn.bytes ? 0 : b;
+}
+
 // Slice parameters of a call and what the rule certified.
 struct Choice {
     int beta = 0, S = 0, band = 0;
@@ -678,8 +688,8 @@ size_t md_gemm_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S)
         ResPanels pn;
         if (take_residues(form, S, b, M, N, K, true, rp, pn))
             bytes = std::max(bytes, small_bytes(M, N) + digits_bytes(MD_FORM_INT8, M, K, 1) +
-                                        digits_bytes(MD_FORM_INT8, N, K, 1) + digits_bytes(MD_FORM_INT8, M, K, rp.SB) +
-                                        digits_bytes(MD_FORM_INT8, N, K, rp.SB) + pn.bytes + 4096);
+                                        digits_bytes(MD_FORM_INT8, N, K, 1) + res_digits(rp, pn, M, N, K) + pn.bytes +
+                                        4096);
     }
     return bytes;
 }
@@ -890,13 +900,14 @@ int gemm_impl(int m, int transA, int transB, int64_t M, int64_t N, int64_t K, co
     {
         ResPlan rp;
         ResPanels pn;
-        void *dA = nullptr, *dB = nullptr, *work = nullptr;
+        void *dig = nullptr, *work = nullptr;
         if (!dbg && take_residues(o.form, S, beta, M, N, K, duo, rp, pn)) {
             const bool cuts = res_cuts(rp, m);   // the evaluation cuts the digits itself: no digit planes
-            const size_t bA = cuts ? 0 : digits_bytes(MD_FORM_INT8, M, K, rp.SB);
-            const size_t bB = cuts ? 0 : digits_bytes(MD_FORM_INT8, N, K, rp.SB);
+            const size_t beside = cuts ? 0 : res_digits(rp, pn, M, N, K);
             const Scratch::Mark before = scr.mark();
-            if (!scr.get(pn.bytes, &work) && (cuts || (!scr.get(bA, &dA) && !scr.get(bB, &dB)))) {
+            if (!scr.get(pn.bytes, &work) && (!beside || !scr.get(beside, &dig))) {
+                char* dA = cuts ? nullptr : beside ? (char*)dig : (char*)work + pn.res_at;
+                char* dB = cuts ? nullptr : dA + digits_bytes(MD_FORM_INT8, M, K, rp.SB);
                 GemmArgs ga;
                 memset(&ga, 0, sizeof(ga));
                 ga.A = dA;

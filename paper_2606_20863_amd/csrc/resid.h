@@ -67,6 +67,8 @@ struct ResPanels {
     int64_t mr = 0, nc = 0;          // multiples of kResTile, or the whole extent
     int bq = 0, nchunk = 0;          // products of the last diagonal per unit, their units
     size_t bytes = 0;                // of one panel's planes, residues and tables
+    size_t res_at = 0;               // from here on the products' residues: free until the products run
+    bool single = false;             // one panel is the whole product
 };
 bool res_panels(const ResPlan& r, int64_t M, int64_t N, int64_t K, ResPanels& p);
 

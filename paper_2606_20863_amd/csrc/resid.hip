@@ -1230,6 +1230,8 @@ bool res_panels(const ResPlan& r, int64_t M, int64_t N, int64_t K, ResPanels& p)
         if (l.total <= kLimit && l.nbA * l.nbB * 256 <= (INT64_C(1) << 27) &&
             T * (r.npp() + p.nchunk) <= 0x7fffffff) {
             p.bytes = l.total;
+            p.res_at = l.R;
+            p.single = p.mr == M && p.nc == N;
             return true;
         }
         int64_t& side = p.mr >= p.nc ? p.mr : p.nc;

@@ -106,3 +106,15 @@ def test_sizes_are_bounded(memory, monkeypatch):
     for k in range(5000):
         md._note_sizes(k, 5, True, lambda S: (S, S))
     assert len(md._SIZES) <= 4096 and 4999 in md._SIZES
+
+
+def test_digit_planes_lie_inside_the_panel():
+    """The benchmark product: 164 residue planes of both operands, 150 planes
+    of the products' residues, two units of the last diagonal's 32-bit sums
+    and one magnitude plane of both operands; 27 digit planes of both are not
+    added to them."""
+    n = 4096
+    full = md.lib().md_gemm_workspace_size(2, n, n, n, 27)
+    assert md.lib().md_gemm_planes(2, n, n, n, 27, 8) == 164
+    planes = 164 * 2 + 150 + 2 * 4 + 2
+    assert planes * n * n < full < (planes + 1) * n * n
