@@ -33,6 +33,7 @@ baseline), ``choose_params``.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -246,9 +247,17 @@ def _auto_workspace(key, sizes_of_S, S, device, stream):
     return None
 
 
+@functools.lru_cache(maxsize=4096)
+def _gemm_size(form, M, N, K, S):
+    """md_gemm_workspace_size: a function of its arguments alone that weighs
+    the ways to contract (1 to 4 us on the host, FP64 digits the most), asked
+    for in every forced or hinted call."""
+    return lib().md_gemm_workspace_size(form, M, N, K, S)
+
+
 def _gemm_sizes(form, M, N, K, S):
     """Scratch sizes of a product, the fastest way's, then the least."""
-    yield lib().md_gemm_workspace_size(form, M, N, K, S)
+    yield _gemm_size(form, M, N, K, S)
     yield lib().md_gemm_workspace_least(form, M, N, K, S)
 
 

@@ -118,3 +118,21 @@ def test_digit_planes_lie_inside_the_panel():
     assert md.lib().md_gemm_planes(2, n, n, n, 27, 8) == 164
     planes = 164 * 2 + 150 + 2 * 4 + 2
     assert planes * n * n < full < (planes + 1) * n * n
+
+
+def test_sizes_are_worked_out_once(memory, monkeypatch):
+    """Forced and hinted calls that repeat a shape do not size its scratch
+    again."""
+    asked = []
+
+    class Library:
+        def md_gemm_workspace_size(self, *args):
+            asked.append(args)
+            return 1000
+
+    monkeypatch.setattr(md, "lib", Library)
+    md._gemm_size.cache_clear()
+    for _ in range(3):
+        md._auto_workspace("shape", lambda S: md._gemm_sizes(0, 64, 64, 64, S), 5, "cpu", None)
+    md._gemm_size.cache_clear()
+    assert len(asked) == 1 and memory.asked == [1000] * 3
