@@ -230,7 +230,9 @@ __device__ __forceinline__ double rn_signed(uint32_t (&L)[NL], int32_t& sg, int&
     return w;
 }
 
-// The same on a sign and magnitude (-1)^neg X 2^scale, X >= 0 in the limbs.
+// The same on a sign and magnitude (-1)^neg X 2^scale, X >= 0 in the limbs:
+// with to_limbs the form in which the host tests put integers to the steps;
+// the kernels hold two's complement (rn_signed, to_limbs_signed).
 template <int NL>
 __device__ __forceinline__ double rn_next(uint32_t (&L)[NL], double& sgn, int& scale)
 {

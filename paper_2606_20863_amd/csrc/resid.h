@@ -35,7 +35,6 @@ namespace mdg {
 
 constexpr int kResMaxPrimes = 8;
 constexpr int kResTile = 256;        // outputs per workgroup side
-constexpr int kResBlock = 32;        // rows per residue fragment (v_mfma_i32_32x32x32_i8)
 
 struct ResPlan {
     int L = 0, N = 0, P = 0;         // coefficients, points, primes

@@ -12,7 +12,6 @@ namespace mdg {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 // the largest primes below 256; eight multiply to 2^62.8
 constexpr int kPrimes[kResMaxPrimes] = {251, 241, 239, 233, 229, 227, 223, 211};
@@ -837,8 +836,10 @@ struct ResFinalArgs {
 // halves' sums meet at the end, each half of the wave keeping every other
 // row (double-doubles 2048^3, 8 primes of 9 points: a step of three products
 // 3216 -> 3050 us).
+// Waves per SIMD: four, three where the LDS (32 KB and one per limb) holds
+// no more, two with two tiles' registers.
 template <int NL, int NT, bool FIX, bool PK>
-__global__ __launch_bounds__(256, NT == 1 ? 4 : 2) void k_res_final(ResFinalArgs a)
+__global__ __launch_bounds__(256, NT == 2 ? 2 : NL <= 8 ? 4 : 3) void k_res_final(ResFinalArgs a)
 {
     __shared__ int64_t coef[4][16][64];
     __shared__ uint32_t limb[4][NL][64];
@@ -1033,14 +1034,21 @@ hipError_t launch_res_final(const ResFinalArgs& a, bool packed, hipStream_t st)
         return hipErrorInvalidValue;
     // two tiles of 16 coefficients at once (four, for L > 32, leave one wave
     // per SIMD: 549 -> 761 us at hexa-double 1024^3)
-    const bool two = a.L > 16;
-    if (a.g.fixX)
-        hipLaunchKernelGGL((two ? k_res_final<NL, 2, true, false> : k_res_final<NL, 1, true, false>), blocks, dim3(256), 0,
-                           st, a);
-    else
-        hipLaunchKernelGGL((two ? k_res_final<NL, 2, false, false> : k_res_final<NL, 1, false, false>), blocks, dim3(256),
-                           0, st, a);
-    return hipGetLastError();
+    if (a.L > 16) {
+        if (a.g.fixX)
+            hipLaunchKernelGGL((k_res_final<NL, 2, true, false>), blocks, dim3(256), 0, st, a);
+        else
+            hipLaunchKernelGGL((k_res_final<NL, 2, false, false>), blocks, dim3(256), 0, st, a);
+        return hipGetLastError();
+    }
+    if constexpr (NL <= 16) {   // up to 16 coefficients of at most 24 bits fold into 14 limbs
+        if (a.g.fixX)
+            hipLaunchKernelGGL((k_res_final<NL, 1, true, false>), blocks, dim3(256), 0, st, a);
+        else
+            hipLaunchKernelGGL((k_res_final<NL, 1, false, false>), blocks, dim3(256), 0, st, a);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
 }
 
 // limbs that hold |X| < K 2^(beta (S + 1) + 1) and its sign, rounded up to
