@@ -1288,10 +1288,13 @@ hipError_t launch_resid(const ResPlan& r, const ResPanels& pn, const GemmArgs& g
 
     const int nl = res_limbs(r, K);
 
-    // A sum v of products of centred residues has |v| <= K (p/2)^2.  The one-
-    // step reduction's quotient is v / p up to half a unit of v's 24-bit
-    // rounding and a relative 2^-25 of 1 / p; it leaves |r| <= p / 2 + both,
-    // which a byte holds up to K = 2048 (p = 251: 125.5 + 1 + 0.96).
+    // A sum v of products of centred residues has |v| <= K ((p-1)/2)^2.  The
+    // one-step reduction's quotient is v / p up to half a unit of v's 24-bit
+    // rounding and the relative error of 1 / p (below 2^-24: 0.50 of it for p =
+    // 251, 0.88 for 241, 0.84 for 223), so it leaves |r| <= p / 2 + 1 + that
+    // error times v.  At K = 2048 that is 127.45 for p = 251, the binding one
+    // (125.5 + 1 + 0.95), and at most 123.1 for the others: over all sums r
+    // reaches 127, and past 2048 depths p = 251 leaves the byte.
     const bool wide = nkr * kKcI8 > 2048;
 
     auto eval = [&](const char* dig, int64_t rows, const int8_t* V, char* out, int64_t plane) {

@@ -135,8 +135,10 @@ __device__ __forceinline__ Placed place_word(double x, int kn, int pad, bool& ne
     const uint64_t v = mant >> t;                   // truncated toward zero below the grid
     const uint32_t P = (uint32_t)((np < 0 ? -np : 0) + pad);
     Placed r;
-    // floor(P / W) as a 24-bit product and shift: exact for P < 2^10
-    // (within the digits of any container here, P < 8 * 64 + 64)
+    // floor(P / W) as a 24-bit product and shift: exact for P < 1448, W from
+    // 56 to 63 (a word within its entry's digits has P <= 8 * 128 - 53 in the
+    // widest container here; the callers clamp the limb index, so a word
+    // beyond, in an entry that breaks the preconditions, stays in the store)
     constexpr uint32_t kMagic = (65536u + W - 1) / W;
     r.j = (int)(__umul24(P, kMagic) >> 16);
     const int o = (int)P - W * r.j;
