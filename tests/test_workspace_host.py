@@ -136,3 +136,17 @@ def test_sizes_are_worked_out_once(memory, monkeypatch):
         md._auto_workspace("shape", lambda S: md._gemm_sizes(0, 64, 64, 64, S), 5, "cpu", None)
     md._gemm_size.cache_clear()
     assert len(asked) == 1 and memory.asked == [1000] * 3
+
+
+def test_the_depth_is_cut_into_parts():
+    """The products of test_gpu_parts.py: what their scratch takes beyond the
+    least is two parts' integers and scales or more."""
+    from test_gpu_parts import CASES
+    for m, form, M, N, K in CASES:
+        for G in (4, 8, 16):
+            beta, S, _, _ = md.choose_params(form, K, 50 * m, G)
+            full, least = md._gemm_sizes(md._FORMS[form], M, N, K, S)
+            assert md.lib().md_gemm_planes(md._FORMS[form], M, N, K, S, beta) == 0
+            words, rest = divmod(full - least - 256, 4 * M * N)
+            parts, one = divmod(words, md.fixed_limbs(beta, S, K))
+            assert rest == 0 and one == 1 and 2 <= parts <= 64, (m, form, M, N, K, S)
