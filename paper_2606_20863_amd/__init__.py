@@ -316,7 +316,8 @@ def gemm_ex(A: torch.Tensor, B: torch.Tensor, C: torch.Tensor | None = None, *, 
     device writes the data's certificate into ``cert`` (``read_cert``).
     ``workspace``: a contiguous device buffer of ``md_gemm_workspace_size``
     bytes, or of at least ``md_gemm_workspace_least`` (the call then allocates
-    nothing).
+    nothing; with the least it multiplies the slices themselves, on the form's
+    own matrix units, where the residue planes take more).
     ``noalloc``: call md_gemm_ex_noalloc (the library's own fixed scratch
     array, no workspace; C must then be given to allocate nothing at all).
     Without a workspace the scratch comes from torch's caching allocator

@@ -26,12 +26,15 @@ static std::map<uintptr_t, size_t> held;
 static uintptr_t next_ptr = 1ull << 40;
 static size_t sum, peak, max_one = ~0ull, max_sum = ~0ull;
 static int launches, refused;
+static uintptr_t last_freed;
+static int out_of_order;
 extern "C" {
 void limits(size_t one, size_t all) { max_one = one; max_sum = all; peak = sum; launches = refused = 0; }
 size_t held_now() { return sum; }
 size_t held_most() { return peak; }
 int launched() { return launches; }
 int refusals() { return refused; }
+int backwards() { return out_of_order; }
 int hipMallocFromPoolAsync(void** p, size_t n, void*, void*)
 {
     if (n > max_one || sum + n > max_sum) { ++refused; return 2; }
@@ -46,6 +49,8 @@ int hipFreeAsync(void* p, void*)
 {
     auto it = held.find((uintptr_t)p);
     if (it == held.end()) abort();
+    out_of_order += (uintptr_t)p < last_freed;
+    last_freed = (uintptr_t)p;
     sum -= it->second;
     held.erase(it);
     return 0;
@@ -164,3 +169,12 @@ print(rc, rt.refusals(), rt.held_now(), most)
 """)
     assert most > 27 * 4096 * (4096 + 32) + 2 * 8 * 4 * 4096 * 24   # parts in the first call
     assert refused == 1 and rc == 0 and rest == 0
+
+
+def test_blocks_are_freed_in_the_order_taken(runtime):
+    rc, back = drive(runtime, """
+rc = call(4, 100, 90, 80, form=2, force_S=27, force_beta=8)
+rc |= call(16, 256, 256, 1024, form=2, s_hint=105, cert=1 << 47, validate=1)
+print(rc, rt.backwards())
+""")
+    assert rc == 0 and back == 0
