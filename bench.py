@@ -16,7 +16,9 @@ digits' residues (md_gemm_planes > 0: this workload in every form) the work
 counted is the INT8 products it runs, 2 M N K times that many planes, and the
 residues' evaluation, interpolation and rounding are inside the time; where it
 multiplies the slices themselves, 2 M N K S(S+1)/2.  Every fraction in the
-output counts work done, of the matrix unit that does it.
+output counts work done, of the matrix unit that does it.  slice_products is
+the same product with the slices multiplied themselves: INT8 slices on the
+INT8 unit against FP64 slices on the FP64 one.
 
 The CPU leg, after all GPU work (skip with --no-cpu), is the only user of
 the oracle: cpu_baseline times the exact C oracle on this host's cores over
@@ -166,14 +168,14 @@ def progress(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def run_form(md, torch, A, B, form, steps, warmup):
+def run_form(md, torch, A, B, form, steps, warmup, workspace=None):
     hip, evs = hip_events(steps)
     for _ in range(warmup):
-        C, info = md.gemm_ex(A, B, form=form)
+        C, info = md.gemm_ex(A, B, form=form, workspace=workspace)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for i in range(steps):
-        C, info = md.gemm_ex(A, B, form=form, events=evs[i])
+        C, info = md.gemm_ex(A, B, form=form, workspace=workspace, events=evs[i])
     info["rule"] = "rho" if info["G"] != info["G_span"] or info["G_rho"] >= 0 else "span"
     torch.cuda.synchronize()
     t1 = time.perf_counter()
@@ -183,6 +185,34 @@ def run_form(md, torch, A, B, form, steps, warmup):
         hip.hipEventDestroy(ctypes.c_void_p(b))
     ms = (t1 - t0) * 1e3 / steps
     return C, info, ms, sum(kern) / len(kern)
+
+
+def slice_products(md, torch, A, B, found, steps=2):
+    """The benchmark product with every form's slices multiplied themselves,
+    each on its own matrix unit (S (S + 1) / 2 products; the slice
+    contractions that the metric's name compares): what the library does on a
+    workspace of md_gemm_workspace_least bytes, which holds no residue planes.
+    ``found``: form -> (C, info) of the default calls, whose words these must
+    be."""
+    M, K = A.shape[1], A.shape[2]
+    N = B.shape[2]
+    flop = 2.0 * M * N * K
+    out = {}
+    for form, (Cd, info) in found.items():
+        S = info["S"]
+        ws = torch.empty(md.lib().md_gemm_workspace_least(md._FORMS[form], M, N, K, S), dtype=torch.uint8,
+                         device=A.device)
+        C, got, ms, kern = run_form(md, torch, A, B, form, steps, 1, workspace=ws)
+        peak = PEAK_FP64_TFLOPS if form == "fp64" else PEAK_INT8_TOPS
+        tops = flop * S * (S + 1) / 2 / (kern * 1e-3) / 1e12
+        out[form] = {"S": got["S"], "steps": steps, "ms_per_call": round(ms, 4), "gemm_kernel_ms": round(kern, 4),
+                     "effective_gflops": round(flop / (ms * 1e-3) / 1e9, 3), "mfma_tops": round(tops, 3),
+                     "peak": peak, "frac_peak": round(tops / peak, 4), "equal_to_default": bool(torch.equal(C, Cd))}
+        del C, ws
+    head = next(iter(found))
+    if "fp64" in out:
+        out["int8_over_fp64"] = round(out["fp64"]["ms_per_call"] / out[head]["ms_per_call"], 3)
+    return out
 
 
 # Sampled outputs of the GPU runs, kept for the CPU leg: the oracle runs
@@ -658,6 +688,9 @@ def main():
     C64, info64, ms64, kern64 = run_form(md, torch, A, B, "fp64", args.fp64_steps, 1)
     progress(f"fp64 form: {ms64:.3f} ms per call")
 
+    slices = slice_products(md, torch, A, B, {head: (C8, info8), "fp64": (C64, info64)})
+    progress(f"slice products: {slices[head]['ms_per_call']:.2f} ms {head}, {slices['fp64']['ms_per_call']:.2f} fp64")
+
     # the ordinary (classical) quad-double product on the same inputs, the
     # paper's comparison baseline; one warm-up and args.ordinary_steps timed
     ord_ms = None
@@ -727,6 +760,7 @@ def main():
                       "max_log2_err_sampled": None,
                       "certified_log2_bound": round(info64["log2_bound"], 2)},
         "int8_over_fp64": round(eff8 / eff64, 3),
+        "slice_products": slices,
         "int8_sign_magnitude_form": None if sm is None else dict(
             int8_summary("int8", sm[1], sm[2], sm[3], args.sm_steps),
             digits="7-bit sign-magnitude digits (the paper's bit-field cut)",
