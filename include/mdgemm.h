@@ -392,9 +392,10 @@ int md_choose_params(int form, int64_t K, int T, int G, int *beta, int *S, int *
 
 /* Scratch bytes with which an md_gemm_ex call of these sizes, form and S
  * runs its fastest way (the residue planes or the depth parts included; up
- * to about 9 GiB).  A call with less runs the slice products, with the same
- * results, as long as it has md_gemm_workspace_least bytes; below that it
- * returns MD_ENOMEM.  With either size a call allocates nothing. */
+ * to about 9 GiB a panel).  With less, what does not fit is left out, with
+ * the same results, down to the slice products on md_gemm_workspace_least
+ * bytes; below that the call returns MD_ENOMEM.  With either size a call
+ * allocates nothing. */
 size_t md_gemm_workspace_size(int form, int64_t M, int64_t N, int64_t K, int S);
 
 /* Scratch bytes that such a call needs at least: those of the slice
