@@ -255,6 +255,12 @@ def _gemm_size(form, M, N, K, S):
     return lib().md_gemm_workspace_size(form, M, N, K, S)
 
 
+@functools.lru_cache(maxsize=4096)
+def _gemm_planes(form, M, N, K, S, beta):
+    """md_gemm_planes, as ``_gemm_size``."""
+    return lib().md_gemm_planes(form, M, N, K, S, beta)
+
+
 def _gemm_sizes(form, M, N, K, S):
     """Scratch sizes of a product, the fastest way's, then the least."""
     yield _gemm_size(form, M, N, K, S)
@@ -272,16 +278,21 @@ def _note_sizes(key, S, ruled, sizes_of_S):
     _SIZES[key] = (seen + (S,) if ruled else (), tuple(map(max, sizes, new)) if seen else new)
 
 
-def _run_with_scratch(call, opts: "MDOpts", ws, key, sizes_of_S, info: "MDInfo"):
-    """call() with ws as the workspace; a call whose slice rule chose a larger
-    S than ws holds stops with MD_ENOMEM before it writes any output, and
-    runs again on the library's pool.  Records the S taken under key."""
+def _call_with_scratch(call, opts: "MDOpts", ws):
     if ws is not None:
         opts.workspace, opts.workspace_bytes = ctypes.c_void_p(ws.data_ptr()), ws.numel()
     rc = call()
     if rc == 5 and ws is not None:
         opts.workspace, opts.workspace_bytes = None, 0
         rc = call()
+    return rc
+
+
+def _run_with_scratch(call, opts: "MDOpts", ws, key, sizes_of_S, info: "MDInfo"):
+    """call() with ws as the workspace; a call whose slice rule chose a larger
+    S than ws holds stops with MD_ENOMEM before it writes any output, and
+    runs again on the library's pool.  Records the S taken under key."""
+    rc = _call_with_scratch(call, opts, ws)
     _check(rc, info)
     _note_sizes(key, info.S, opts.force_S <= 0 and opts.s_hint <= 0, sizes_of_S)
     return rc
@@ -574,10 +585,20 @@ def gemm_fixed(A: torch.Tensor, B: torch.Tensor, E: torch.Tensor | None = None,
         if flags.dtype != torch.int32 or not flags.is_cuda or flags.numel() < 1:
             raise ValueError("flags must be an int32 device tensor")
         opts.exp_flags = ctypes.c_void_p(flags.data_ptr())
-    rc = lib().md_gemm_fixed(m, M, N, K, pa, lda, psa, pb, ldb, psb,
-                             None if E is None else _ptr(E), None if F is None else _ptr(F),
-                             _ptr(X), nlimb, _ptr(scale), ctypes.byref(opts), _stream_handle(stream))
-    _check(rc, info)
+    sh = _stream_handle(stream)
+
+    def call():
+        return lib().md_gemm_fixed(m, M, N, K, pa, lda, psa, pb, ldb, psb,
+                                   None if E is None else _ptr(E), None if F is None else _ptr(F),
+                                   _ptr(X), nlimb, _ptr(scale), ctypes.byref(opts), sh)
+
+    # residue planes in torch's scratch (the pool gives panels above 4 GiB
+    # back after every call: quad-doubles 4096^3 12.1 ms on it); the other
+    # ways, which may also hold the diagonal sums, on the library's pool
+    ws = None
+    if _gemm_planes(_FORMS[form], M, N, K, S, beta):
+        ws = _auto_workspace(None, lambda S: (_gemm_size(_FORMS[form], M, N, K, S),), S, A.device, stream)
+    _check(_call_with_scratch(call, opts, ws), info)
     return X, scale, info.as_dict()
 
 
